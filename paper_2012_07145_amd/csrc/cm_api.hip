@@ -174,6 +174,7 @@ void free_model(cm::Model &m)
 {
     if (m.d_params) (void)hipFree(m.d_params);
     if (m.d_beta) (void)hipFree(m.d_beta);
+    if (m.d_fp32) (void)hipFree(m.d_fp32);
     if (m.d_bf16) (void)hipFree(m.d_bf16);
     if (m.d_fp8) (void)hipFree(m.d_fp8);
     delete[] m.h_params;
@@ -280,7 +281,9 @@ cm_status cm_model_create(const cm_model_desc *d, const float *params, cm_model 
     cm_model *M = new (std::nothrow) cm_model;
     if (!M) return fail(CM_ENOMEM, "host allocation failed");
     Model &m = M->m;
-    if (hipGetDevice(&m.device) != hipSuccess) {
+    if (hipGetDevice(&m.device) != hipSuccess ||
+        hipDeviceGetAttribute(&m.cus, hipDeviceAttributeMultiprocessorCount, m.device) !=
+            hipSuccess) {
         delete M;
         return fail(CM_EDEVICE, "no HIP device");
     }
@@ -338,6 +341,24 @@ cm_status cm_model_create(const cm_model_desc *d, const float *params, cm_model 
     }
     for (int mo = 0; mo < C; ++mo) pk.b2[mo] = params[OFF_B2 + mo];
 
+    Fp32Pack p32;
+    std::memset(&p32, 0, sizeof p32);
+    for (int lane = 0; lane < 64; ++lane) {
+        const int m = lane & 15, g = lane >> 4;
+        float w[40] = {};
+        for (int hh = 0; hh < 2; ++hh) {
+            const int row = 16 * hh + m;
+            for (int t = 0; t < 10; ++t)
+                if (row < E) w[10 * hh + t] = Ws[row * FS + 4 * t + g];
+            for (int t = 0; t < 6; ++t) w[20 + 6 * hh + t] = W1[row * 2 * E + E + 4 * t + g];
+        }
+        for (int t = 0; t < 8; ++t)
+            if (m < C) w[32 + t] = W2[m * H + 4 * t + g];
+        for (int v = 0; v < 10; ++v) std::memcpy(&p32.w[v][lane], w + 4 * v, 16);
+    }
+    std::memcpy(p32.bs, bs, E * sizeof(float));
+    std::memcpy(p32.b2, params + OFF_B2, C * sizeof(float));
+
     m.h_params = new (std::nothrow) float[N_PARAMS];
     if (!m.h_params) {
         delete M;
@@ -347,6 +368,7 @@ cm_status cm_model_create(const cm_model_desc *d, const float *params, cm_model 
     cm_status st;
     if ((st = dev_alloc(&m.d_params, N_PARAMS, "parameters")) != CM_OK ||
         (st = dev_alloc(&m.d_beta, H, "beta")) != CM_OK ||
+        (st = dev_alloc(&m.d_fp32, 1, "float32 operands")) != CM_OK ||
         (st = dev_alloc(&m.d_bf16, 1, "bf16 operands")) != CM_OK) {
         free_model(m);
         delete M;
@@ -355,6 +377,7 @@ cm_status cm_model_create(const cm_model_desc *d, const float *params, cm_model 
     if (hipMemcpy(m.d_params, params, N_PARAMS * sizeof(float), hipMemcpyHostToDevice) !=
             hipSuccess ||
         hipMemcpy(m.d_beta, beta, sizeof beta, hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(m.d_fp32, &p32, sizeof p32, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(m.d_bf16, &pk, sizeof pk, hipMemcpyHostToDevice) != hipSuccess) {
         free_model(m);
         delete M;
@@ -456,14 +479,12 @@ void fill_eval_launch(cm::EvalLaunch &L, const cm_batch *b, int32_t g0, int32_t 
         r += b->queries[g0 + j].n_stages;
         order[j] = j;
     }
-    if (prec != CM_FP32) {
-        auto per_wave = [&](int32_t j) {
-            const int S = b->queries[g0 + j].n_stages;
-            return (S + stage_parts(S) - 1) / stage_parts(S);
-        };
-        std::stable_sort(order, order + ng,
-                         [&](int32_t x, int32_t y) { return per_wave(x) > per_wave(y); });
-    }
+    auto per_wave = [&](int32_t j) {
+        const int S = b->queries[g0 + j].n_stages;
+        return prec == CM_FP32 ? S : (S + stage_parts(S) - 1) / stage_parts(S);
+    };
+    std::stable_sort(order, order + ng,
+                     [&](int32_t x, int32_t y) { return per_wave(x) > per_wave(y); });
     int64_t hrow = 0, task = 0;
     for (int32_t jj = 0; jj < ng; ++jj) {
         const int32_t j = order[jj];
@@ -482,7 +503,7 @@ void fill_eval_launch(cm::EvalLaunch &L, const cm_batch *b, int32_t g0, int32_t 
         e.stage_off = Q.terms_off / C;
         hrow += Q.n_stages;
         if (prec == CM_FP32) {
-            task += cdiv(Q.n_cands, 64);
+            task += cdiv(Q.n_cands, FP32_TILE);
         } else {
             const int64_t tiles = cdiv(Q.n_cands, TILE_ROWS);
             task += cdiv(tiles, EVAL_WAVES / e.parts);

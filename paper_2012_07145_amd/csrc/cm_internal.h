@@ -30,6 +30,7 @@ static_assert(N_PARAMS == CM_N_PARAMS, "parameter layout");
 constexpr int QMAX = 32;            // queries per kernel launch (descriptors by value)
 constexpr int TILE_ROWS = 32;       // candidates per wave of the bf16 evaluator
 constexpr int EVAL_WAVES = 8;       // waves per workgroup of the bf16 evaluator
+constexpr int FP32_TILE = 16;       // candidates per tile of the float32 evaluator
 
 // Stage parts of the bf16 evaluator: a query's stages are split into P
 // contiguous, near-equal parts, one wave each; the parts' compensated sums
@@ -63,6 +64,17 @@ struct Bf16Pack {
 };
 static_assert(offsetof(Bf16Pack, logtab) % 16 == 0, "table copied in 16-byte units");
 
+// Operands of the float32 evaluator's three layers, laid out as the 16x16x4
+// float32 matrix core reads them: value v of lane l is row l % 16, term
+// 4t + l / 16 of a step t.  Values 0..19: W_s rows 0..15 (10 steps), then
+// 16..23; 20..31: W_1[:, 24:] rows 0..15 (6 steps), then 16..31; 32..39: W_2
+// (8 steps).  Rows past a layer's end are 0.
+struct Fp32Pack {
+    float4 w[10][64];
+    float4 bs[8];  // b_s, zeros past 24
+    float4 b2[4];  // b_2, zeros past 8
+};
+
 // e4m3 operands of the FP8 form, laid out as the 32x32x64 fp8 matrix core
 // reads them (32 bytes per lane and operand), and its scales.
 struct Fp8Pack {
@@ -77,8 +89,10 @@ struct Fp8Pack {
 
 struct Model {
     int device = 0;
+    int cus = 0;                 // compute units of the device
     float *d_params = nullptr;   // float32 blob as given
     float *d_beta = nullptr;     // W_1[:, 24:] b_s (32), added when folding
+    Fp32Pack *d_fp32 = nullptr;  // packed operands of the float32 evaluator
     Bf16Pack *d_bf16 = nullptr;  // packed operands of the bf16 evaluator
     Fp8Pack *d_fp8 = nullptr;    // operands of the FP8 form (after cm_model_prepare_fp8)
     float fp8_uscale = 0.f;      // Fp8Pack::uh, kept on the host for the hoist
@@ -100,7 +114,7 @@ struct EvalQ {
     int64_t pipe_off, sched_off, terms_off, cost_off;
     int64_t u_off;     // offset (floats) of this query's hoisted rows U[S][32]
     int32_t hrow0;     // first hoist block of this query in the launch
-    int32_t task0;     // first workgroup (bf16) or thread block (fp32) of this query
+    int32_t task0;     // first workgroup task of this query
     int32_t parts;     // stage parts P (bf16)
     int32_t pad;
     int64_t stage_off; // offset (floats) of this query's per-stage costs [S][N] (terms_off / 8)
@@ -108,7 +122,7 @@ struct EvalQ {
 
 struct EvalLaunch {
     int32_t nq;
-    int32_t ntasks;    // workgroups (bf16) or thread blocks (fp32)
+    int32_t ntasks;    // row-tile groups (bf16, FP8) or tiles (fp32)
     int32_t nstages;   // hoist blocks
     int32_t pad;
     EvalQ q[QMAX];

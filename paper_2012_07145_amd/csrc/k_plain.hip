@@ -7,11 +7,13 @@
 // plus W_1[:, 24:] b_s when the evaluator folds the schedule embedding into
 // the first layer, times the hidden scale s_h of the FP8 form (1 else).
 //
-// Float32 evaluator: one thread per candidate walks the stages in ascending
-// order, computing log1p of the 40 schedule features, the schedule embedding,
-// the ReLU layer on the stacked embeddings, the ReLU coefficient layer and the
-// dot product with the 8 cost terms (Sec. 5.2, App. B), and keeps a
-// Kahan-compensated float32 sum over stages.
+// Float32 evaluator: log1p of the 40 schedule features, the schedule
+// embedding, the ReLU layer on the stacked embeddings, the ReLU coefficient
+// layer and the dot product with the 8 cost terms (Sec. 5.2, App. B), on the
+// float32 matrix cores, and a Kahan-compensated float32 sum over stages in
+// ascending order.
+#include <algorithm>
+
 #include "cm_internal.h"
 
 namespace cm {
@@ -98,72 +100,249 @@ __global__ __launch_bounds__(64) void k_hoist_step(const StepHead *__restrict__ 
     }
 }
 
-__global__ __launch_bounds__(64) void k_eval_fp32(EvalLaunch L, const float *__restrict__ params,
-                                                  const float *__restrict__ sched,
-                                                  const float *__restrict__ terms,
-                                                  const float *__restrict__ U,
-                                                  float *__restrict__ cost,
-                                                  float *__restrict__ stage)
+// ---- float32 evaluator ----
+// Every sum is the same chain of fused multiply-adds, in the same order, that
+// a scalar walk over features, embedding and hidden units gives: one
+// 16x16x4 float32 matrix instruction adds four consecutive terms of the chain
+// in ascending order, rounding each (compared bit for bit with the fmaf chain
+// over a million sums, subnormal ones included).  So the layers stay
+// unfolded: bs + Ws x, then u + W1 es, then b2 + W2 h.
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Packed layer operands held by a lane for the whole launch (lane l: row
+// l % 16, term 4t + l / 16 of step t) and its part of the accumulator seeds
+// (rows 4 (l / 16) .. +3).
+struct Fp32Weights {
+    float ws[2][10], w1[2][6], w2[8];
+    f32x4 bs[2], b2;
+};
+
+__device__ inline Fp32Weights load_fp32(const Fp32Pack *__restrict__ pk, int lane)
 {
-    const int q = find_query(L, blockIdx.x, false);
-    const EvalQ Q = L.q[q];
-    const int i = (blockIdx.x - Q.task0) * 64 + threadIdx.x;
-    if (i >= Q.N) return;
-
-    const float *Ws = params + OFF_WS;
-    const float *bs = params + OFF_BS;
-    const float *W1 = params + OFF_W1;
-    const float *W2 = params + OFF_W2;
-    const float *b2 = params + OFF_B2;
-
-    float sum = 0.f, comp = 0.f;
-    for (int s = 0; s < Q.S; ++s) {
-        const int64_t r = (int64_t)s * Q.N + i;
-        const float4 *xr = reinterpret_cast<const float4 *>(sched + Q.sched_off + r * FS);
-        float x[FS];
+    float w[40];
 #pragma unroll
-        for (int v = 0; v < FS / 4; ++v) {
-            float4 t4 = xr[v];
-            x[4 * v + 0] = log1pf(t4.x);
-            x[4 * v + 1] = log1pf(t4.y);
-            x[4 * v + 2] = log1pf(t4.z);
-            x[4 * v + 3] = log1pf(t4.w);
-        }
-        float es[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) {
-            float a = bs[e];
-#pragma unroll
-            for (int f = 0; f < FS; ++f) a = fmaf(Ws[e * FS + f], x[f], a);
-            es[e] = a;
-        }
-        const float *u = U + Q.u_off + (int64_t)s * H;
-        float h[H];
-#pragma unroll
-        for (int j = 0; j < H; ++j) {
-            float a = u[j];
-#pragma unroll
-            for (int e = 0; e < E; ++e) a = fmaf(W1[j * 2 * E + E + e], es[e], a);
-            h[j] = a < 0.f ? 0.f : a;  // ReLU; a NaN passes through
-        }
-        const float *tr = terms + Q.terms_off + r * C;
-        float v = 0.f;
-#pragma unroll
-        for (int m = 0; m < C; ++m) {
-            float a = b2[m];
-#pragma unroll
-            for (int j = 0; j < H; ++j) a = fmaf(W2[m * H + j], h[j], a);
-            const float c = a < 0.f ? 0.f : a;
-            v = fmaf(c, tr[m], v);
-        }
-        if (stage) stage[Q.stage_off + r] = v;
-        // Kahan-compensated stage sum
-        const float y = v - comp;
-        const float t = sum + y;
-        comp = (t - sum) - y;
-        sum = t;
+    for (int v = 0; v < 10; ++v) {
+        const float4 x = pk->w[v][lane];
+        w[4 * v] = x.x;
+        w[4 * v + 1] = x.y;
+        w[4 * v + 2] = x.z;
+        w[4 * v + 3] = x.w;
     }
-    cost[Q.cost_off + i] = sum;
+    Fp32Weights W;
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+#pragma unroll
+        for (int t = 0; t < 10; ++t) W.ws[hh][t] = w[10 * hh + t];
+#pragma unroll
+        for (int t = 0; t < 6; ++t) W.w1[hh][t] = w[20 + 6 * hh + t];
+    }
+#pragma unroll
+    for (int t = 0; t < 8; ++t) W.w2[t] = w[32 + t];
+    const int g = lane >> 4;
+    const float4 s0 = pk->bs[g], s1 = pk->bs[4 + g], s2 = pk->b2[g];
+    W.bs[0] = f32x4{s0.x, s0.y, s0.z, s0.w};
+    W.bs[1] = f32x4{s1.x, s1.y, s1.z, s1.w};
+    W.b2 = f32x4{s2.x, s2.y, s2.z, s2.w};
+    return W;
+}
+
+__device__ inline f32x4 mfma4(float a, float b, f32x4 c)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ inline void swap32(float &a, float &b)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+
+__device__ inline void swap16(float &a, float &b)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
+                                                    false);
+    a = __uint_as_float(r[0]);
+    b = __uint_as_float(r[1]);
+}
+
+// A layer's output tile (lane group g = lane / 16 holds rows 4g .. 4g+3 of
+// its column) as the next layer's operands: step t's operand is row 4t + g,
+// the transpose of the 4 x 4 (group, register) grid.
+__device__ inline void transpose4(f32x4 &v)
+{
+    float a = v[0], b = v[1], c = v[2], d = v[3];
+    swap32(a, c);
+    swap32(b, d);
+    swap16(a, b);
+    swap16(c, d);
+    v = f32x4{a, b, c, d};
+}
+
+__device__ inline float relu32(float a) { return a < 0.f ? 0.f : a; }  // a NaN passes through
+
+__device__ inline __amdgpu_buffer_rsrc_t rows_at(const float *p, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), (short)0, bytes, 0x00020000);
+}
+
+// One stage of 16 candidates: x = the raw features 4t + g of candidate
+// lane % 16, u = the stage's hoisted units 4g .. +3 and 16 + 4g .. +3, tr =
+// cost terms 4g .. 4g+3 of that candidate (g < 2).  Returns the stage's cost
+// in lanes 16..31.
+__device__ __forceinline__ float stage32(const float (&x)[10], const f32x4 (&u)[2], const f32x4 &tr,
+                                         const Fp32Weights &W)
+{
+    f32x4 e0 = W.bs[0], e1 = W.bs[1];
+#pragma unroll
+    for (int t = 0; t < 10; ++t) {
+        const float l = log1pf(x[t]);
+        e0 = mfma4(W.ws[0][t], l, e0);
+        e1 = mfma4(W.ws[1][t], l, e1);
+    }
+    transpose4(e0);
+    transpose4(e1);
+    f32x4 h0 = u[0], h1 = u[1];
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+        const float e = t < 4 ? e0[t] : e1[t - 4];
+        h0 = mfma4(W.w1[0][t], e, h0);
+        h1 = mfma4(W.w1[1][t], e, h1);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        h0[j] = relu32(h0[j]);
+        h1[j] = relu32(h1[j]);
+    }
+    transpose4(h0);
+    transpose4(h1);
+    f32x4 c = W.b2;
+#pragma unroll
+    for (int t = 0; t < 8; ++t) c = mfma4(W.w2[t], t < 4 ? h0[t] : h1[t - 4], c);
+    // coefficients 0..3 of the chain in lane group 0, then 4..7 in group 1
+    float v = 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v = fmaf(relu32(c[j]), tr[j], v);
+    float w = v;
+    swap16(v, w);  // v: group 0's partial sum in groups 0 and 1
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v = fmaf(relu32(c[j]), tr[j], v);
+    return v;
+}
+
+constexpr int F32_WAVES = 8;     // waves per workgroup
+constexpr int F32_CHUNK = 128;   // stages between two rounds of summing
+constexpr int F32_ROW = FS * 4;  // bytes of a feature row
+
+struct Fp32Shared {
+    uint4 xs[F32_WAVES][FP32_TILE * F32_ROW / 16];  // one stage's feature rows of each wave
+    float v[2][F32_CHUNK][FP32_TILE];               // stage costs of two chunks
+    float2 carry[FP32_TILE];                        // (sum, compensation) between chunks
+};
+
+// Loads of one wave's stage, issued one stage ahead of its arithmetic: the
+// tile's 16 feature rows (2,560 contiguous bytes) straight into the wave's
+// LDS block as whole cache lines, terms and hoisted units into registers.
+__device__ __forceinline__ void issue32(const EvalQ &Q, const float *sched, const float *terms,
+                                        const float *U, int s, int i0, int rows, int lane,
+                                        uint4 *xsw, f32x4 (&u)[2], f32x4 &tr)
+{
+    constexpr int NT = 2;  // non-temporal: read exactly once
+    const int64_t r = (int64_t)s * Q.N + i0;
+    const auto xr = rows_at(sched + Q.sched_off + r * FS, rows * F32_ROW);
+    const auto tq = rows_at(terms + Q.terms_off + r * C, rows * C * 4);
+    const int g = lane >> 4, n = lane & 15;
+    tr = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                       tq, n * (C * 4) + (g & 1) * 16, 0, NT));
+    const float4 *ur = reinterpret_cast<const float4 *>(U + Q.u_off + (int64_t)s * H);
+    u[0] = __builtin_bit_cast(f32x4, ur[g]);
+    u[1] = __builtin_bit_cast(f32x4, ur[4 + g]);
+    const int vo = lane * 16;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)xsw, 16, vo, 0, 0, NT);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(xsw + 64), 16, vo + 1024, 0, 0, NT);
+    if (lane < 32)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (lds_void *)(xsw + 128), 16, vo + 2048, 0, 0,
+                                                 NT);
+}
+static_assert(FP32_TILE * F32_ROW == 2560, "three copies of 1,024 + 1,024 + 512 bytes");
+
+// A workgroup takes tiles of 16 candidates; its waves share a tile's stages
+// (wave w: w, w + 8, ...), write the stage costs to LDS, and one wave, a
+// different one for each chunk of stages, adds them in ascending order with
+// compensation while the others go on.
+// Bound by the vector ALU: log1pf is about 75 instructions a value (300 cycles
+// a wave and SIMD), 10 values a lane and stage, against 40 matrix
+// instructions of 32 cycles.  One query of 30 x 6,400: 515 us with one thread
+// per candidate (100 waves, each a serial walk over the stages), 38 us so;
+// 4 x 64: 80 us and 11 us.
+__global__ __launch_bounds__(F32_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+k_eval_fp32(EvalLaunch L, const Fp32Pack *__restrict__ pk, const float *sched, const float *terms,
+            const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage)
+{
+    __shared__ Fp32Shared sh;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int g = lane >> 4, n = lane & 15;
+    const Fp32Weights W = load_fp32(pk, lane);
+    uint4 *xsw = sh.xs[wave];
+    const float *xw = reinterpret_cast<const float *>(xsw);
+    int round = 0;
+    for (int task = blockIdx.x; task < L.ntasks; task += gridDim.x) {
+        const int q = find_query(L, task, false);
+        const EvalQ &Q = L.q[q];
+        const int i0 = (task - Q.task0) * FP32_TILE;
+        const int rows = min(FP32_TILE, Q.N - i0);
+        for (int c0 = 0; c0 < Q.S; c0 += F32_CHUNK, ++round) {
+            const int c1 = min(c0 + F32_CHUNK, Q.S);
+            float(*vb)[FP32_TILE] = sh.v[round & 1];
+            f32x4 u[2], tr;
+            if (c0 + wave < c1) issue32(Q, sched, terms, U, c0 + wave, i0, rows, lane, xsw, u, tr);
+            for (int s = c0 + wave; s < c1; s += F32_WAVES) {
+                // the copy has landed (the compiler's own waits need not see
+                // this read of the block)
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                float x[10];
+#pragma unroll
+                for (int t = 0; t < 10; ++t) x[t] = xw[n * FS + 4 * t + g];
+                // the rows are in registers before the block is refilled
+                asm volatile("" ::"v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]),
+                             "v"(x[6]), "v"(x[7]), "v"(x[8]), "v"(x[9])
+                             : "memory");
+                f32x4 u0[2] = {u[0], u[1]}, t0 = tr;
+                if (s + F32_WAVES < c1)
+                    issue32(Q, sched, terms, U, s + F32_WAVES, i0, rows, lane, xsw, u, tr);
+                asm volatile("" ::: "memory");
+                const float v = stage32(x, u0, t0, W);
+                if (g == 1) {
+                    vb[s - c0][n] = v;
+                    if (stage && n < rows) stage[Q.stage_off + (int64_t)s * Q.N + i0 + n] = v;
+                }
+            }
+            __syncthreads();
+            // the chunk's sum; the next chunk's stage costs go to the other
+            // buffer, and this wave reaches the next barrier only after it
+            if (wave == (round & (F32_WAVES - 1)) && lane < FP32_TILE) {
+                float sum = 0.f, comp = 0.f;
+                if (c0) {
+                    sum = sh.carry[lane].x;
+                    comp = sh.carry[lane].y;
+                }
+                const int m = c1 - c0;
+#pragma unroll 8
+                for (int s = 0; s < m; ++s) {
+                    const float y = vb[s][lane] - comp;
+                    const float t = sum + y;
+                    comp = (t - sum) - y;
+                    sum = t;
+                }
+                if (c1 < Q.S) sh.carry[lane] = make_float2(sum, comp);
+                else if (lane < rows) cost[Q.cost_off + i0 + lane] = sum;
+            }
+        }
+    }
 }
 
 }  // namespace
@@ -191,7 +370,9 @@ hipError_t launch_eval_fp32(const EvalLaunch &L, const Model &m, const float *sc
                             hipStream_t st)
 {
     if (L.ntasks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_eval_fp32, dim3(L.ntasks), dim3(64), 0, st, L, m.d_params, sched,
+    // two workgroups of 8 waves fill a compute unit (4 waves per SIMD)
+    const int grid = std::min(L.ntasks, 2 * m.cus);
+    hipLaunchKernelGGL(k_eval_fp32, dim3(grid), dim3(F32_WAVES * 64), 0, st, L, m.d_fp32, sched,
                        terms, U, cost, stage);
     return hipGetLastError();
 }

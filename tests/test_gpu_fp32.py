@@ -1,0 +1,59 @@
+"""Float32 evaluator on the GPU at the edges of its work split: tiles of 16
+candidates, stages shared by 8 waves, sums carried over chunks of 128 stages,
+and more tiles than the grid's workgroups -- costs and per-stage costs against
+the oracle.
+
+Tolerance: a coefficient is a chain of at most 40 + 24 + 32 float32 fused
+multiply-adds whose terms' magnitudes add up to at most about 20 for these
+weights (hidden units of up to 10 against 32 weights of variance 1/32), so
+its error stays below 96 * 2^-24 * 20 = 1.1e-4, and a stage's or query's cost
+error below that times the sum of its cost terms.  The typical candidate is
+held to 1e-6 relative.
+"""
+import numpy as np
+import pytest
+
+from synth import draw_query, model_params
+from tests import gpucase as gc
+
+pytestmark = pytest.mark.gpu
+
+COEF_TOL, MEDIAN_TOL = 1.1e-4, 1e-6
+
+SHAPES = [
+    [(1, 1)], [(7, 15)], [(8, 16)], [(9, 17)],
+    [(127, 16), (128, 17), (129, 33), (300, 5)],   # chunk edges, several queries
+    [(2, 9700), (130, 20), (1, 31)],               # more tiles than workgroups
+]
+
+
+@pytest.mark.parametrize("shapes", SHAPES, ids=lambda s: "+".join(f"{a}x{b}" for a, b in s))
+def test_fp32_split_edges(oracle_mod, shapes):
+    import torch
+    import paper_2012_07145_amd as cm
+    rng = np.random.default_rng(sum(a * 7919 + b for a, b in shapes))
+    params = model_params(bias=True)
+    m = cm.cm_model_create(params)
+    qs = [draw_query(rng, S, N) for S, N in shapes]
+    ws = gc.workspace_for(cm, qs)
+    batch, cost = cm.pack_queries(qs, "fp32")
+    rows = sum(q.n_stages * q.n_cands for q in qs)
+    stage = torch.full((rows + 4,), -7.0, device="cuda")
+    cm.cm_eval_batch(m, "fp32", batch, ws, cost)
+    plain = cost.clone()
+    cost.fill_(-3.0)
+    cm.cm_eval_stages(m, "fp32", batch, ws, cost, stage)
+    torch.cuda.synchronize()
+    assert torch.equal(plain, cost)
+    assert (stage[rows:] == -7.0).all()
+    c, st = cost.cpu().numpy(), stage.cpu().numpy()
+    for q, d in zip(qs, batch.queries):
+        S, N = q.n_stages, q.n_cands
+        ref, refs = oracle_mod.eval_query(params, q.pipe, q.sched, q.terms, stage_costs=True)
+        tsum = q.terms.astype(np.float64).sum(axis=2)
+        got = st[d[4] // 8:d[4] // 8 + S * N].reshape(S, N).astype(np.float64)
+        assert np.all(np.abs(got - refs) <= COEF_TOL * tsum), (S, N)
+        mine = c[d[5]:d[5] + N].astype(np.float64)
+        assert np.all(np.abs(mine - ref) <= COEF_TOL * tsum.sum(axis=0)), (S, N)
+        assert np.median(gc.rel_err(mine, ref)) <= MEDIAN_TOL, (S, N)
+    ws.close()
