@@ -172,10 +172,7 @@ cm_status dev_alloc(T **p, size_t count, const char *what)
 
 void free_model(cm::Model &m)
 {
-    if (m.d_params) (void)hipFree(m.d_params);
-    if (m.d_beta) (void)hipFree(m.d_beta);
-    if (m.d_fp32) (void)hipFree(m.d_fp32);
-    if (m.d_bf16) (void)hipFree(m.d_bf16);
+    if (m.d) (void)hipFree(m.d);
     if (m.d_fp8) (void)hipFree(m.d_fp8);
     delete[] m.h_params;
     m = cm::Model{};
@@ -292,20 +289,21 @@ cm_status cm_model_create(const cm_model_desc *d, const float *params, cm_model 
     // scaled by ln 2 because the evaluator feeds log2(1 + x).
     const float *Ws = params + OFF_WS, *bs = params + OFF_BS;
     const float *W1 = params + OFF_W1, *W2 = params + OFF_W2;
-    float beta[H];
+    ModelData md;
+    std::memset(&md, 0, offsetof(ModelData, bf16) + offsetof(Bf16Pack, logtab));
+    std::memcpy(md.params, params, sizeof md.params);
     double Wf[H][FS];
     for (int j = 0; j < H; ++j) {
         double b = 0.0;
         for (int e = 0; e < E; ++e) b += (double)W1[j * 2 * E + E + e] * (double)bs[e];
-        beta[j] = (float)b;
+        md.beta[j] = (float)b;
         for (int f = 0; f < FS; ++f) {
             double a = 0.0;
             for (int e = 0; e < E; ++e) a += (double)W1[j * 2 * E + E + e] * (double)Ws[e * FS + f];
             Wf[j][f] = a * 0.69314718055994530942;
         }
     }
-    Bf16Pack pk;
-    std::memset(&pk, 0, sizeof pk);
+    Bf16Pack &pk = md.bf16;
     // operands of the 16x16x32 bf16 matrix core: lane l holds row l % 16 and
     // k-slots 8g .. 8g+7, g = l / 16
     for (int hh = 0; hh < 2; ++hh)
@@ -341,8 +339,7 @@ cm_status cm_model_create(const cm_model_desc *d, const float *params, cm_model 
     }
     for (int mo = 0; mo < C; ++mo) pk.b2[mo] = params[OFF_B2 + mo];
 
-    Fp32Pack p32;
-    std::memset(&p32, 0, sizeof p32);
+    Fp32Pack &p32 = md.fp32;
     for (int lane = 0; lane < 64; ++lane) {
         const int m = lane & 15, g = lane >> 4;
         float w[40] = {};
@@ -366,25 +363,19 @@ cm_status cm_model_create(const cm_model_desc *d, const float *params, cm_model 
     }
     std::memcpy(m.h_params, params, N_PARAMS * sizeof(float));
     cm_status st;
-    if ((st = dev_alloc(&m.d_params, N_PARAMS, "parameters")) != CM_OK ||
-        (st = dev_alloc(&m.d_beta, H, "beta")) != CM_OK ||
-        (st = dev_alloc(&m.d_fp32, 1, "float32 operands")) != CM_OK ||
-        (st = dev_alloc(&m.d_bf16, 1, "bf16 operands")) != CM_OK) {
+    if ((st = dev_alloc(&m.d, 1, "model")) != CM_OK) {
         free_model(m);
         delete M;
         return st;
     }
-    if (hipMemcpy(m.d_params, params, N_PARAMS * sizeof(float), hipMemcpyHostToDevice) !=
-            hipSuccess ||
-        hipMemcpy(m.d_beta, beta, sizeof beta, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(m.d_fp32, &p32, sizeof p32, hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(m.d_bf16, &pk, sizeof pk, hipMemcpyHostToDevice) != hipSuccess) {
+    if (hipMemcpy(m.d, &md, offsetof(ModelData, bf16) + offsetof(Bf16Pack, logtab),
+                  hipMemcpyHostToDevice) != hipSuccess) {
         free_model(m);
         delete M;
         return fail(CM_EDEVICE, "copy of model parameters failed");
     }
     // the log-transform table of the bf16 evaluator, computed by the device
-    if (cm::launch_log_table(m.d_bf16, nullptr) != hipSuccess ||
+    if (cm::launch_log_table(&m.d->bf16, nullptr) != hipSuccess ||
         hipStreamSynchronize(nullptr) != hipSuccess) {
         (void)hipGetLastError();
         free_model(m);
@@ -828,11 +819,11 @@ cm_status cm_topk_per_query(const float *cost, const cm_batch *b, int32_t k, cm_
             t.out_q = g0 + j;
             t.cost_off = Q.cost_off;
             t.tile0 = (int32_t)tile;
-            t.ntiles = (int32_t)std::max<int64_t>(1, cdiv(Q.n_cands, TOPK_TILE));
+            t.ntiles = (int32_t)std::max<int64_t>(1, cdiv(Q.n_cands, TOPK_CALL_TILE));
+            L.max_tiles = std::max(L.max_tiles, t.ntiles);
             tile += t.ntiles;
         }
         if (tile * k > w.tpart_cap) return fail(CM_E2BIG, "batch exceeds workspace beam lists");
-        L.ntasks = (int32_t)tile;
         CM_HIP(launch_topk(L, cost, w.d_tpart, w.d_tcnt, idx_out, val_out, s));
     }
     return CM_OK;

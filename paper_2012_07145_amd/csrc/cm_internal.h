@@ -40,7 +40,8 @@ __host__ __device__ constexpr int stage_parts(int S)
 {
     return S <= CM_STAGE_CHUNK / 2 ? 1 : S <= CM_STAGE_CHUNK ? 2 : S <= 2 * CM_STAGE_CHUNK ? 4 : 8;
 }
-constexpr int TOPK_TILE = 4096;     // candidates per workgroup of the selection
+constexpr int TOPK_TILE = 4096;     // candidates per selection tile of the step kernel
+constexpr int TOPK_CALL_TILE = 16384; // candidates per tile of the selection kernel
 
 // bf16 split-product operands of the two dense layers, laid out as the
 // 16x16x32 bf16 matrix-core instruction reads them: 8 bf16 (16 bytes) per
@@ -87,13 +88,21 @@ struct Fp8Pack {
     float pad;
 };
 
+// Everything a model holds on the device from its creation, filled by one
+// copy (the log table by a kernel after it).
+struct ModelData {
+    float params[N_PARAMS];  // float32 blob as given
+    float beta[H];           // W_1[:, 24:] b_s, added when folding
+    Fp32Pack fp32;           // packed operands of the float32 evaluator
+    Bf16Pack bf16;           // packed operands of the bf16 evaluator
+};
+static_assert(offsetof(ModelData, fp32) % 16 == 0 && offsetof(ModelData, bf16) % 16 == 0,
+              "operands are read in 16-byte units");
+
 struct Model {
     int device = 0;
     int cus = 0;                 // compute units of the device
-    float *d_params = nullptr;   // float32 blob as given
-    float *d_beta = nullptr;     // W_1[:, 24:] b_s (32), added when folding
-    Fp32Pack *d_fp32 = nullptr;  // packed operands of the float32 evaluator
-    Bf16Pack *d_bf16 = nullptr;  // packed operands of the bf16 evaluator
+    ModelData *d = nullptr;
     Fp8Pack *d_fp8 = nullptr;    // operands of the FP8 form (after cm_model_prepare_fp8)
     float fp8_uscale = 0.f;      // Fp8Pack::uh, kept on the host for the hoist
     float *h_params = nullptr;   // host copy of the blob (FP8 preparation, calibration)
@@ -164,7 +173,7 @@ struct TopkQ {
 
 struct TopkLaunch {
     int32_t nq;
-    int32_t ntasks;
+    int32_t max_tiles; // most tiles of a query
     int32_t k;
     int32_t pad;
     TopkQ q[QMAX];

@@ -72,16 +72,16 @@ hipError_t launch_eval_bf16(const EvalLaunch &L, const Model &m, const uint16_t 
     const dim3 g(L.ntasks), b(EVAL_WAVES * 64);
     if (ridx) {
         if (stage)
-            hipLaunchKernelGGL((k_eval_bf16<true, true>), g, b, 0, st, L, m.d_bf16, sched, terms,
+            hipLaunchKernelGGL((k_eval_bf16<true, true>), g, b, 0, st, L, &m.d->bf16, sched, terms,
                                U, cost, stage, ridx, rows);
         else
-            hipLaunchKernelGGL((k_eval_bf16<false, true>), g, b, 0, st, L, m.d_bf16, sched, terms,
+            hipLaunchKernelGGL((k_eval_bf16<false, true>), g, b, 0, st, L, &m.d->bf16, sched, terms,
                                U, cost, stage, ridx, rows);
     } else if (stage) {
-        hipLaunchKernelGGL((k_eval_bf16<true, false>), g, b, 0, st, L, m.d_bf16, sched, terms, U,
+        hipLaunchKernelGGL((k_eval_bf16<true, false>), g, b, 0, st, L, &m.d->bf16, sched, terms, U,
                            cost, stage, ridx, rows);
     } else {
-        hipLaunchKernelGGL((k_eval_bf16<false, false>), g, b, 0, st, L, m.d_bf16, sched, terms, U,
+        hipLaunchKernelGGL((k_eval_bf16<false, false>), g, b, 0, st, L, &m.d->bf16, sched, terms, U,
                            cost, stage, ridx, rows);
     }
     return hipGetLastError();

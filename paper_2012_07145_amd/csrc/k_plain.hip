@@ -351,7 +351,7 @@ hipError_t launch_hoist(const EvalLaunch &L, const Model &m, bool fold, float sc
                         const float *pipe, float *U, hipStream_t st)
 {
     if (L.nstages == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_hoist, dim3(L.nstages), dim3(64), 0, st, L, m.d_params, m.d_beta,
+    hipLaunchKernelGGL(k_hoist, dim3(L.nstages), dim3(64), 0, st, L, m.d->params, m.d->beta,
                        fold ? 1 : 0, scale, pipe, U);
     return hipGetLastError();
 }
@@ -360,7 +360,7 @@ hipError_t launch_step_hoist(const StepHead *h, const StepQ *qs, const Model &m,
                              cm_precision prec, int grid, hipStream_t st)
 {
     const float *scale = prec == CM_FP8 ? &m.d_fp8->uh : nullptr;
-    hipLaunchKernelGGL(k_hoist_step, dim3(grid), dim3(64), 0, st, h, qs, m.d_params, m.d_beta,
+    hipLaunchKernelGGL(k_hoist_step, dim3(grid), dim3(64), 0, st, h, qs, m.d->params, m.d->beta,
                        scale);
     return hipGetLastError();
 }
@@ -372,7 +372,7 @@ hipError_t launch_eval_fp32(const EvalLaunch &L, const Model &m, const float *sc
     if (L.ntasks == 0) return hipSuccess;
     // two workgroups of 8 waves fill a compute unit (4 waves per SIMD)
     const int grid = std::min(L.ntasks, 2 * m.cus);
-    hipLaunchKernelGGL(k_eval_fp32, dim3(grid), dim3(F32_WAVES * 64), 0, st, L, m.d_fp32, sched,
+    hipLaunchKernelGGL(k_eval_fp32, dim3(grid), dim3(F32_WAVES * 64), 0, st, L, &m.d->fp32, sched,
                        terms, U, cost, stage);
     return hipGetLastError();
 }

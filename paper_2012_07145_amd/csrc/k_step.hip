@@ -31,10 +31,13 @@ __device__ __forceinline__ void select_tile(const StepQ &D, int q, int tile, int
                             uint64_t *tpart, TopkShared<NT> &tsh, int &s_query_last)
 {
     const int tid = threadIdx.x;
-    uint64_t key[TopkShared<NT>::PER];
+    constexpr int PER = TOPK_TILE / NT;
+    uint32_t ord[PER];
     int nvalid;
-    tile_keys<NT, true>(D.cost, D.N, tile, key, nvalid);
-    int nbest = tile_select<NT>(key, nvalid, k, tsh);
+    tile_orders<NT, PER, true>(D.cost, D.N, tile * TOPK_TILE, ord, nvalid);
+    int nbest = tile_select<NT, PER>(
+        ord, [&](int j) { return (uint32_t)(tile * TOPK_TILE + j * NT + sel_tid()); }, nvalid, k,
+        tsh);
     bool write = true;
     if (D.ntiles > 1) {
         publish_list<NT>(tsh, nbest, k, tpart + (int64_t)(D.tile0 + tile) * k);
@@ -44,7 +47,7 @@ __device__ __forceinline__ void select_tile(const StepQ &D, int q, int tile, int
         write = s_query_last;
         if (write) {
             if (tid == 0) atomicExch(&qcnt[q], 0u);
-            nbest = merge_lists<NT>(tpart + (int64_t)D.tile0 * k, D.ntiles, D.N, k, tsh);
+            nbest = merge_lists<NT, PER>(tpart + (int64_t)D.tile0 * k, D.ntiles, TOPK_TILE, D.N, k, tsh);
         }
     }
     if (write) {
@@ -219,7 +222,7 @@ hipError_t launch_step(const StepHead *h, const StepQ *qs, uint32_t *ctl, uint64
         hipLaunchKernelGGL(k_step_fp8, dim3(grid), dim3(NT), 0, st, h, qs, ctl, tpart, m.d_fp8);
     else
         hipLaunchKernelGGL(k_step_bf16, dim3(grid), dim3(NT), 0, st, h, qs, ctl, tpart,
-                           m.d_bf16);
+                           &m.d->bf16);
     return hipGetLastError();
 }
 

@@ -8,19 +8,28 @@
 // ranks after +inf, so the unsigned order of the keys is exactly "ascending
 // cost, ties by lower index, NaN last", and keys are unique.
 //
-// One workgroup of NT threads selects over a tile of up to TOPK_TILE
-// candidates (TOPK_TILE / NT keys per thread, element e = j*NT + thread):
-//   1. every thread takes the minimum of its keys; the k-th smallest of these
-//      NT minima (a bitonic sort of the minima across the workgroup) is a
-//      threshold T with at least k keys <= T (the k minima themselves), and
-//      for unordered costs only slightly more than k;
-//   2. keys <= T are compacted into LDS with one atomic per wave and key slot;
-//   3. each compacted key is placed by counting the compacted keys below it;
-//      keys placed at rank < k are the k best, already in order.
-// If more than 1024 keys pass the threshold (only possible for large k), a
-// workgroup-wide bitwise radix search over them takes the place of step 3.
+// One workgroup of NT threads selects over a tile of up to NT * PER
+// candidates (element e = j*NT + thread):
+//   1. every lane takes the minimum of its keys' cost halves; each wave whose
+//      lanes all hold a candidate finds the m-th smallest of its 64 minima,
+//      m = ceil(k / waves), by m wave minima; the largest of these is a
+//      threshold with at least k keys at or under it, and for unordered costs
+//      a few times k (tiles of at most max(128, 2k) candidates skip this: all
+//      pass; in a larger one the full waves hold at least k keys);
+//   2. keys under it are compacted into LDS, one atomic per wave;
+//   3. each compacted key is placed by counting the compacted keys below it
+//      (up to 8 threads share a key's count); keys placed at rank < k are the
+//      k best, already in order.
+// If more than FILT keys pass (many equal costs, costs in an order that
+// defeats the threshold, large k), a workgroup-wide bitwise radix search for
+// the exact k-th key takes the place of the threshold.
 // A query with several tiles has each tile's sorted k best written to a
 // device list; the last tile to finish selects again over those lists.
+// All of it is latency: a chain of about six barriers.  The threshold by a
+// bitonic sort of one 64-bit minimum per thread (36 exchanges, three of them
+// through LDS) that this replaced made the selection of 6,400 candidates
+// 18.5 us in two tiles of 4,096, against 5.7 us in one of 16,384, and
+// of 17 queries of up to 4,096 12.4 us against 6.5 us.
 #pragma once
 
 #include "cm_internal.h"
@@ -28,32 +37,34 @@
 namespace cm {
 namespace topk {
 
-constexpr uint64_t SENT = ~0ull;  // empty slot: ranks after every real key
-constexpr int RANK_MAX = 1024;  // largest compacted set placed by counting
-static_assert(TOPK_TILE > CM_MAX_K, "a merge pass must make progress");
+constexpr uint64_t SENT = ~0ull;      // empty slot: ranks after every real key
+constexpr uint32_t EMPTY = ~0u;       // its cost half
+constexpr int FILT = 1024;            // compacted keys placed by counting
+constexpr int ALL_PASS = 128;         // tiles of at most this many keys skip the threshold
+static_assert(FILT > CM_MAX_K && FILT >= 2 * CM_MAX_K, "a merge round makes progress, all may pass");
 
-__device__ inline uint64_t make_key(float c, uint32_t idx)
+// Order-preserving image of a cost.
+__device__ inline uint32_t cost_order(float c)
 {
     uint32_t b = __float_as_uint(c);
     const uint32_t mag = b & 0x7fffffffu;
     if (mag == 0) b = 0;                          // -0 -> +0
     else if (mag > 0x7f800000u) b = 0x7fc00000u;  // any NaN -> one quiet NaN
-    b = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-    return ((uint64_t)b << 32) | idx;
+    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// NT = threads of the workgroup that selects (256 or 512); element e of a
-// tile is held by thread e % NT as its key e / NT.
+__device__ inline uint64_t make_key(uint32_t order, uint32_t idx)
+{
+    return ((uint64_t)order << 32) | idx;
+}
+
 template <int NT>
 struct TopkShared {
     static constexpr int WAVES = NT / 64;
-    static constexpr int PER = TOPK_TILE / NT;
-    static_assert(PER * NT == TOPK_TILE, "tile split");
     static_assert(NT >= CM_MAX_K, "one thread per output slot");
-    uint64_t mins[NT];
-    uint64_t filt[TOPK_TILE];
+    uint64_t filt[FILT];
     uint64_t best[CM_MAX_K];
-    uint64_t thr;
+    uint32_t thr[WAVES];
     uint32_t nfilt;
     uint32_t cnt[2][WAVES];
     uint32_t red_and[WAVES], red_or[WAVES];
@@ -62,7 +73,7 @@ struct TopkShared {
 __device__ inline uint32_t wave_count(bool p) { return (uint32_t)__popcll(__ballot(p)); }
 
 // The thread's index, opaque to the compiler: values derived from it (lane
-// masks, partner addresses of the sort) are recomputed where they are used
+// masks, partner addresses) are recomputed where they are used
 // instead of being hoisted out of the persistent kernel's task loop, where
 // they would stay live through the evaluation and spill.
 __device__ inline int sel_tid()
@@ -72,42 +83,41 @@ __device__ inline int sel_tid()
     return t;
 }
 
-// ---------------------------------------------------------------- sorting
-__device__ inline uint64_t shfl_xor64(uint64_t v, int mask)
+// ---------------------------------------------------------------- waves
+template <int CTRL>
+__device__ inline uint32_t dpp(uint32_t v)
 {
-    const int lo = __shfl_xor((int)(uint32_t)v, mask);
-    const int hi = __shfl_xor((int)(uint32_t)(v >> 32), mask);
-    return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, true);
+}
+constexpr int QUAD_XOR1 = 0xB1, QUAD_XOR2 = 0x4E, HALF_MIRROR = 0x141, MIRROR = 0x140;
+
+// Minimum over the wave, in every lane: pairs, quads (lane ^ 1, ^ 2), then
+// mirrored halves and rows of 16 lanes, then rows.
+__device__ inline uint32_t wave_min(uint32_t v)
+{
+    v = min(v, dpp<QUAD_XOR1>(v));
+    v = min(v, dpp<QUAD_XOR2>(v));
+    v = min(v, dpp<HALF_MIRROR>(v));
+    v = min(v, dpp<MIRROR>(v));
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = min((uint32_t)r[0], (uint32_t)r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return min((uint32_t)h[0], (uint32_t)h[1]);
 }
 
-// Ascending bitonic sort of one key per thread across the NT-thread
-// workgroup: thread t returns the key of rank t.  Pairs closer than a wave
-// exchange by shuffles; farther ones through x (NT keys of LDS).
+// Room for this wave's n keys in the compacted set (n uniform): its first slot.
 template <int NT>
-__device__ uint64_t block_sort1(uint64_t key, uint64_t *x)
+__device__ inline uint32_t reserve(TopkShared<NT> &sh, uint32_t n, int lane)
 {
-    const int t = sel_tid();
-#pragma unroll
-    for (int size = 2; size <= NT; size <<= 1) {
-#pragma unroll
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            uint64_t other;
-            if (stride >= 64) {
-                x[t] = key;
-                __syncthreads();
-                other = x[t ^ stride];
-                __syncthreads();
-            } else {
-                other = shfl_xor64(key, stride);
-            }
-            const bool up = (t & size) == 0;       // this run ascends
-            const bool lower = (t & stride) == 0;  // t is the first of its pair
-            const uint64_t mn = key < other ? key : other;
-            const uint64_t mx = key < other ? other : key;
-            key = lower == up ? mn : mx;
-        }
-    }
-    return key;
+    uint32_t base = 0;
+    if (lane == 0 && n) base = atomicAdd(&sh.nfilt, n);
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+}
+
+__device__ inline uint32_t lanes_below(uint64_t mask)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
 // ---------------------------------------------------------------- workgroup
@@ -175,103 +185,122 @@ __device__ uint32_t block_radix(const uint32_t (&val)[PER], const bool (&sel)[PE
     return prefix;
 }
 
-// Threshold over the compacted keys when too many passed to place by counting.
-template <int NT>
-__device__ uint64_t block_threshold(int nf, uint32_t rank, TopkShared<NT> &sh)
+// The k-th smallest key of the workgroup's registers (at least k real ones).
+template <int NT, int PER, class Index>
+__device__ uint64_t block_threshold(const uint32_t (&ord)[PER], Index index, int k,
+                                    TopkShared<NT> &sh)
 {
-    constexpr int PER = TopkShared<NT>::PER;
     int buf = 0;
-    uint32_t hi[PER], lo[PER];
+    uint32_t rank = (uint32_t)k, idx[PER];
     bool sel[PER], eq[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int e = j * NT + sel_tid();
-        const uint64_t key = e < nf ? sh.filt[e] : SENT;
-        hi[j] = (uint32_t)(key >> 32);
-        lo[j] = (uint32_t)key;
-        sel[j] = key != SENT;
+        sel[j] = ord[j] != EMPTY;
+        idx[j] = (uint32_t)index(j);
     }
-    const uint32_t thi = block_radix(hi, sel, rank, sh, buf);
+    const uint32_t thi = block_radix<NT, PER>(ord, sel, rank, sh, buf);
     uint32_t c = 0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        eq[j] = sel[j] && hi[j] == thi;
+        eq[j] = sel[j] && ord[j] == thi;
         c += wave_count(eq[j]);
     }
     const uint32_t neq = block_sum(c, sh, buf);
-    const uint32_t tlo = neq > rank ? block_radix(lo, eq, rank, sh, buf) : 0xffffffffu;
+    const uint32_t tlo = neq > rank ? block_radix<NT, PER>(idx, eq, rank, sh, buf) : 0xffffffffu;
     return ((uint64_t)thi << 32) | tlo;
 }
 
-// Select the k smallest keys of the workgroup (element e = j*NT + thread;
-// the nvalid real keys occupy elements 0..nvalid-1, the rest are SENT) into
-// sh.best, ascending.  Returns min(k, nvalid).
+// The compacted keys filt[0, n) in order: the min(n, k) smallest into
+// sh.best, by counting.  Ends with a barrier.
 template <int NT>
-__device__ int tile_select(const uint64_t (&key)[TopkShared<NT>::PER], int nvalid, int k,
-                           TopkShared<NT> &sh)
+__device__ int place(int n, int k, TopkShared<NT> &sh)
 {
-    constexpr int PER = TopkShared<NT>::PER;
     const int t = sel_tid();
-    const int lane = t & 63;
-    if (t == 0) sh.nfilt = 0;
-    uint64_t T = SENT - 1;  // at most k keys: all of them
-    if (nvalid > k) {
-        uint64_t m = key[0];
-#pragma unroll
-        for (int j = 1; j < PER; ++j) m = key[j] < m ? key[j] : m;
-        // min(nvalid, NT) >= k + 1 threads hold a real key, so the minimum of
-        // rank k - 1 is a real key
-        m = block_sort1<NT>(m, sh.mins);
-        if (t == k - 1) sh.thr = m;
-    }
-    __syncthreads();
-    if (nvalid > k) T = sh.thr;
-    // compact the keys <= T
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const bool p = key[j] <= T && key[j] != SENT;
-        const uint64_t mask = __ballot(p);
-        if (mask) {
-            const int first = __ffsll((unsigned long long)mask) - 1;
-            uint32_t base = 0;
-            if (lane == first) base = atomicAdd(&sh.nfilt, (uint32_t)__popcll(mask));
-            base = (uint32_t)__shfl((int)base, first);
-            if (p) {
-                const uint32_t below = (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-                sh.filt[base + below] = key[j];
-            }
-        }
-    }
-    __syncthreads();
-    const int nf = (int)sh.nfilt;
-    if (nf > RANK_MAX) {
-        // many ties at the threshold's cost: exact threshold over the compacted set
-        const uint64_t T2 = block_threshold(nf, (uint32_t)k, sh);
-        __syncthreads();
-        if (t == 0) sh.nfilt = 0;
-        __syncthreads();
-        uint64_t mine[PER];
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int e = j * NT + t;
-            mine[j] = e < nf ? sh.filt[e] : SENT;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (mine[j] <= T2 && mine[j] != SENT) sh.filt[atomicAdd(&sh.nfilt, 1u)] = mine[j];
-        __syncthreads();
-    }
-    const int n = min((int)sh.nfilt, RANK_MAX);
-    // place by counting; ranks >= k are dropped
-    for (int e = t; e < n; e += NT) {
-        const uint64_t mine = sh.filt[e];
-        int r = 0;
-        for (int j = 0; j < n; ++j) r += sh.filt[j] < mine;
-        if (r < k) sh.best[r] = mine;
+    int lper = 0;  // 1, 2, 4 or 8 neighbouring threads share a key's count
+    while (lper < 3 && (n << (lper + 1)) <= NT) ++lper;
+    const int per = 1 << lper, sub = t & (per - 1);
+    for (int base = 0; base < n; base += NT >> lper) {
+        const int e = base + (t >> lper);
+        const uint64_t mine = e < n ? sh.filt[e] : SENT;
+        uint32_t r = 0;
+#pragma unroll 4
+        for (int j = sub; j < n; j += per) r += sh.filt[j] < mine;
+        if (lper > 0) r += dpp<QUAD_XOR1>(r);
+        if (lper > 1) r += dpp<QUAD_XOR2>(r);
+        if (lper > 2) r += dpp<HALF_MIRROR>(r);
+        if (sub == 0 && e < n && r < (uint32_t)k) sh.best[r] = mine;
     }
     __syncthreads();
     return min(n, k);
+}
+
+// Select the k smallest keys of the workgroup into sh.best, ascending:
+// element j*NT + thread has cost order ord[j] and candidate index(j); the
+// nvalid first elements are real, the others EMPTY.  Returns min(k, nvalid).
+template <int NT, int PER, class Index>
+__device__ int tile_select(const uint32_t (&ord)[PER], Index index, int nvalid, int k,
+                           TopkShared<NT> &sh)
+{
+    const int t = sel_tid();
+    const int lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (t == 0) sh.nfilt = 0;
+    uint32_t T = EMPTY - 1;  // every real key
+    if (nvalid > max(ALL_PASS, 2 * k)) {
+        const int full = min(NT, nvalid) / 64;  // waves that hold a key in every lane
+        uint32_t w = 0;
+        if (wave < full) {
+            uint32_t m = ord[0];
+#pragma unroll
+            for (int j = 1; j < PER; ++j) m = min(m, ord[j]);
+            for (int i = (k + full - 1) / full; i > 0; --i) {  // at most 64
+                w = wave_min(m);
+                if (m == w) m = EMPTY;
+            }
+        }
+        if (lane == 0) sh.thr[wave] = w;
+        __syncthreads();
+        T = 0;
+#pragma unroll
+        for (int j = 0; j < NT / 64; ++j) T = max(T, sh.thr[j]);
+        // 64 minima with repeats run out before m of them are taken
+        T = min(T, EMPTY - 1);
+    } else {
+        __syncthreads();
+    }
+    // compact the keys at or under T
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (j * NT >= nvalid) break;
+        mine += wave_count(ord[j] <= T);
+    }
+    uint32_t base = reserve(sh, mine, lane);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (j * NT >= nvalid) break;
+        const bool p = ord[j] <= T;
+        const uint64_t mask = __ballot(p);
+        const uint32_t pos = base + lanes_below(mask);
+        if (p && pos < FILT) sh.filt[pos] = make_key(ord[j], index(j));
+        base += (uint32_t)__popcll(mask);
+    }
+    __syncthreads();
+    int n = (int)sh.nfilt;
+    if (n > FILT) {
+        const uint64_t T2 = block_threshold<NT, PER>(ord, index, k, sh);
+        __syncthreads();
+        if (t == 0) sh.nfilt = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const uint64_t key = make_key(ord[j], index(j));
+            if (ord[j] != EMPTY && key <= T2) sh.filt[atomicAdd(&sh.nfilt, 1u)] = key;
+        }
+        __syncthreads();
+        n = k;  // keys are unique: exactly k are at or under the k-th
+    }
+    return place<NT>(n, k, sh);
 }
 
 // This workgroup's tile list for the merge: k sorted keys (SENT past nbest),
@@ -285,60 +314,58 @@ __device__ inline void publish_list(const TopkShared<NT> &sh, int nbest, int k, 
 }
 
 // Select again over `ntiles` sorted per-tile lists of k keys at src (every
-// list but the last is full; the last holds min(k, N - (ntiles - 1) *
-// TOPK_TILE) real keys; written by other workgroups with store_shared) into
-// sh.best.  Returns min(k, N).
-template <int NT>
-__device__ int merge_lists(const uint64_t *src, int ntiles, int N, int k, TopkShared<NT> &sh)
+// list but the last is full; the last holds min(k, N - (ntiles - 1) * tile)
+// real keys; written by other workgroups with store_shared) into sh.best.
+// Returns min(k, N).
+template <int NT, int PER>
+__device__ int merge_lists(const uint64_t *src, int ntiles, int tile, int N, int k,
+                           TopkShared<NT> &sh)
 {
-    constexpr int PER = TopkShared<NT>::PER;
     const int t = sel_tid();
-    const int total = ntiles * k;
-    const int total_valid = (ntiles - 1) * k + min(k, N - (ntiles - 1) * TOPK_TILE);
-    const int fresh = TOPK_TILE - k;
+    const int total = (ntiles - 1) * k + min(k, N - (ntiles - 1) * tile);
     int nbest = 0;
-    uint64_t key[PER];
-    for (int base = 0; base < total; base += fresh) {
-        const int nnew = max(0, min(fresh, total_valid - base));
+    for (int base = 0; base < total;) {
+        // the best so far, then as many new keys as fit
+        const int nnew = min(total - base, NT * PER - nbest);
+        uint32_t ord[PER], idx[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int e = j * NT + t;
-            if (e < nbest)
-                key[j] = sh.best[e];
-            else if (e < nbest + nnew)
-                key[j] = load_shared(src + base + e - nbest);
-            else
-                key[j] = SENT;
+            uint64_t key = SENT;
+            if (e < nbest) key = sh.best[e];
+            else if (e < nbest + nnew) key = load_shared(src + base + e - nbest);
+            ord[j] = (uint32_t)(key >> 32);
+            idx[j] = (uint32_t)key;
         }
-        __syncthreads();
-        nbest = tile_select<NT>(key, nbest + nnew, k, sh);
+        __syncthreads();  // best is read
+        nbest = tile_select<NT, PER>(ord, [&](int j) { return idx[j]; }, nbest + nnew, k, sh);
+        base += nnew;
     }
     return nbest;
 }
 
-// Keys of tile `tile` of a query's costs c[0..N) (kShared: written by other
-// workgroups of the same launch).
-template <int NT, bool kShared>
-__device__ inline void tile_keys(const float *c, int N, int tile, uint64_t (&key)[TopkShared<NT>::PER],
-                                 int &nvalid)
+// Cost orders of tile `beg`, beg + 1, ... of a query's costs c[0..N)
+// (kShared: written by other workgroups of the same launch).
+template <int NT, int PER, bool kShared>
+__device__ inline void tile_orders(const float *c, int N, int beg, uint32_t (&ord)[PER],
+                                   int &nvalid)
 {
-    constexpr int PER = TopkShared<NT>::PER;
-    const int beg = tile * TOPK_TILE;
-    nvalid = max(0, min(TOPK_TILE, N - beg));
+    nvalid = max(0, min(NT * PER, N - beg));
+    float v[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         const int e = j * NT + sel_tid();
-        if (e < nvalid) {
-            const float v = kShared ? load_shared(c + beg + e) : c[beg + e];
-            key[j] = make_key(v, (uint32_t)(beg + e));
-        } else {
-            key[j] = SENT;
-        }
+        v[j] = 0.f;
+        if (e < nvalid) v[j] = kShared ? load_shared(c + beg + e) : c[beg + e];
     }
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        ord[j] = j * NT + sel_tid() < nvalid ? cost_order(v[j]) : EMPTY;
 }
 
 // Write the beam: idx[j] = query-local index, val[j] = its cost bit for bit,
-// padded with (-1, +inf) past nbest.
+// padded with (-1, +inf) past nbest.  The cost is its key's, except a zero or
+// NaN, whose bits the key does not keep.
 template <int NT, bool kShared>
 __device__ inline void write_beam(const TopkShared<NT> &sh, int nbest, int k, const float *c,
                                   int32_t *idx, float *val)
@@ -348,8 +375,11 @@ __device__ inline void write_beam(const TopkShared<NT> &sh, int nbest, int k, co
         int32_t id = -1;
         float v = __builtin_inff();
         if (t < nbest) {
-            id = (int32_t)(uint32_t)sh.best[t];
-            v = kShared ? load_shared(c + id) : c[id];
+            const uint64_t key = sh.best[t];
+            const uint32_t o = (uint32_t)(key >> 32);
+            id = (int32_t)(uint32_t)key;
+            v = __uint_as_float((o & 0x80000000u) ? o & 0x7fffffffu : ~o);
+            if (v == 0.f || v != v) v = kShared ? load_shared(c + id) : c[id];
         }
         idx[t] = id;
         val[t] = v;
