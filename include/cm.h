@@ -231,7 +231,7 @@ cm_status cm_eval_stages(const cm_model *model, cm_precision precision,
  * lower index.
  *
  * A sampler owns the device scratch for up to max_queries queries and
- * max_options options per call (about 60 bytes per option).  For query q of
+ * max_options options per call (about 55 bytes per option).  For query q of
  * `batch` (only n_cands = its option count and cost_off are read),
  * hashes[cost_off + i] (device uint64) is option i's structural hash; the
  * representatives' indices are written ascending to sel_idx[cost_off + j]

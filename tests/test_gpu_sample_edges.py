@@ -1,0 +1,81 @@
+"""Hierarchical sampling (cm_sample_buckets) at the edges of its work split:
+chunks of 1,024 options, lists of whole buckets (up to 32 members) and of
+candidates, the hash value that marks an empty slot, and buckets whose
+candidate list comes out short; bit-exact against the oracle, several calls on
+one sampler."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_sample import bucket_hashes, check, run
+
+pytestmark = pytest.mark.gpu
+
+FULL = np.uint64(2 ** 64 - 1)
+
+
+@pytest.fixture(scope="module")
+def cm():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2012_07145_amd as cm
+    return cm
+
+
+@pytest.mark.parametrize("n", [1, 2, 511, 1023, 1024, 1025, 2049, 9000])
+@pytest.mark.parametrize("kind", ["distinct", "equal", "marker", "dense", "low"])
+def test_sample_chunk_edges(cm, oracle_mod, n, kind):
+    rng = np.random.default_rng(n)
+    h = {"distinct": rng.permutation(n).astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15),
+         "equal": np.full(n, 12345, np.uint64),
+         "marker": np.where(rng.random(n) < 0.5, FULL, np.uint64(7)),
+         "dense": rng.integers(0, max(1, n // 100) + 1, n).astype(np.uint64),
+         "low": rng.integers(0, 2 * n, n).astype(np.uint64)}[kind]
+    sp = cm.cm_sampler_create(2, n)
+    for seed in (5, 6):  # the second call finds the table as the first left it
+        sel, cnt, descs = run(cm, sp, [h], [seed])
+        check(oracle_mod, [h], [seed], sel, cnt, descs)
+        assert sel[-1] == -5
+    sp.close()
+
+
+def test_sample_bucket_sizes(cm, oracle_mod):
+    """Buckets of every size at which the representatives or the list change."""
+    rng = np.random.default_rng(3)
+    sizes = [1, 2, 3, 4, 5, 8, 9, 31, 32, 33, 34, 64, 65, 128, 129, 255, 256, 257, 1024, 1025, 4000]
+    parts = [np.repeat(rng.integers(0, 2 ** 64, 20, dtype=np.uint64), b) for b in sizes]
+    hashes = [rng.permutation(p) for p in parts] + [rng.permutation(np.concatenate(parts))]
+    seeds = rng.integers(0, 2 ** 64, len(hashes), dtype=np.uint64)
+    sp = cm.cm_sampler_create(len(hashes), sum(h.size for h in hashes))
+    sel, cnt, descs = run(cm, sp, hashes, seeds)
+    check(oracle_mod, hashes, seeds, sel, cnt, descs)
+    sp.close()
+
+
+# (bucket size, seed) for which fewer members than representatives fall under
+# the bound of the candidates (found by a search over 6e7 seeds)
+SHORT = [(256, 3359416), (256, 6203968), (200, 6634266), (512, 29459833)]
+
+
+def test_sample_short_candidate_lists(cm, oracle_mod):
+    hashes = [np.full(b, 99, np.uint64) for b, _ in SHORT]
+    seeds = np.array([s for _, s in SHORT], np.uint64)
+    # the bucket's options come first, so their keys are the search's
+    rng = np.random.default_rng(4)
+    hashes = [np.concatenate([h, bucket_hashes(rng, 3000)]) for h in hashes]
+    sp = cm.cm_sampler_create(len(hashes), sum(h.size for h in hashes))
+    sel, cnt, descs = run(cm, sp, hashes, seeds)
+    check(oracle_mod, hashes, seeds, sel, cnt, descs)
+    sp.close()
+
+
+def test_sample_many_queries_some_empty(cm, oracle_mod):
+    rng = np.random.default_rng(5)
+    sizes = [0, 0, 3] + [int(rng.integers(0, 2500)) for _ in range(190)] + [0, 1, 0]
+    hashes = [bucket_hashes(rng, n) if n else np.zeros(0, np.uint64) for n in sizes]
+    seeds = rng.integers(0, 2 ** 64, len(sizes), dtype=np.uint64)
+    sp = cm.cm_sampler_create(200, sum(sizes))
+    for part in (slice(None), slice(60, 70), slice(0, 2)):
+        hs, ss = hashes[part], seeds[part]
+        sel, cnt, descs = run(cm, sp, hs, ss)
+        check(oracle_mod, hs, ss, sel, cnt, descs)
+    sp.close()
