@@ -82,25 +82,78 @@ __device__ inline uint32_t encode4(float4 x, float s)
     return lo | (hi << 16);
 }
 
-// n values, 16 per thread (one 16-byte store of codes); the last thread
-// handles the tail one value at a time.
-__global__ __launch_bounds__(256) void k_fp8_encode(const float *__restrict__ x, int64_t n,
-                                                     float s, uint8_t *__restrict__ codes)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int ENC_THREADS = 256;
+constexpr int ENC_PER = 4;                                // quads of values per thread
+constexpr int ENC_TILE = ENC_THREADS * ENC_PER * 4;       // values per workgroup and round
+constexpr uint32_t ENC_LIMIT = 0x71800000u;               // bits of 2^100
+
+// encode4 for values with bits below ENC_LIMIT (+0 <= x < 2^100) and a scale
+// of at most 2^13, the same codes with fewer instructions: no NaN, no
+// negative result and no huge u - 1 to select for, and where u == 1 (x at
+// most 2^-24, a code of 0 at such a scale) the product is 0.  sl = ln 2 * s:
+// a power of two scales every product alike.
+__device__ inline float log1p_scaled(float x, float sl)
 {
-    const int64_t n16 = n / 16;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const float4 *x4 = reinterpret_cast<const float4 *>(x);
-    uint4 *c4 = reinterpret_cast<uint4 *>(codes);
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n16; g += stride) {
-        uint4 o;
-        o.x = encode4(x4[g * 4 + 0], s);
-        o.y = encode4(x4[g * 4 + 1], s);
-        o.z = encode4(x4[g * 4 + 2], s);
-        o.w = encode4(x4[g * 4 + 3], s);
-        c4[g] = o;
+    const float u = 1.f + x;
+    const float d = fmaxf(u - 1.f, 0x1p-24f);
+    return (__builtin_amdgcn_logf(u) * sl) * (x * __builtin_amdgcn_rcpf(d));
+}
+
+__device__ inline uint32_t encode4_plain(f32x4 x, float sl)
+{
+    float y[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        y[j] = __builtin_amdgcn_fmed3f(log1p_scaled(x[j], sl), 0.f, 448.f);
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(
+        y[2], y[3], __builtin_amdgcn_cvt_pk_fp8_f32(y[0], y[1], 0, false), true);
+}
+
+// n values in whole tiles, a quad of values (one 16-byte load, one 4-byte
+// store) per thread and step, so that a wave's loads and stores are
+// contiguous; the last workgroup takes the values past the last tile.  Bound
+// by memory (5 bytes a value) only while the arithmetic stays under about 100
+// cycles a wave and value: a wave whose values are all plain (features are
+// counts and ratios) takes the short form.  The features are read once
+// (non-temporal), the codes are the evaluator's next input (kept in the
+// caches).  168 M values: 127 us (6.6 TB/s) against 157 us with 64 contiguous bytes
+// per thread and the general form for every value.  A workgroup per tile:
+// 8,192 workgroups that loop take 5% more, non-temporal stores 8%.
+__global__ __launch_bounds__(ENC_THREADS) void k_fp8_encode(const float *__restrict__ x, int64_t n,
+                                                            float s, float sl,
+                                                            uint8_t *__restrict__ codes)
+{
+    const int64_t tiles = n / ENC_TILE;
+    const f32x4 *x4 = reinterpret_cast<const f32x4 *>(x);
+    uint32_t *c4 = reinterpret_cast<uint32_t *>(codes);
+    const int t = threadIdx.x;
+    for (int64_t g = blockIdx.x; g < tiles; g += gridDim.x) {
+        const int64_t v0 = g * (ENC_TILE / 4) + t;
+        f32x4 v[ENC_PER];
+        uint32_t most = 0;
+#pragma unroll
+        for (int j = 0; j < ENC_PER; ++j)
+            v[j] = __builtin_nontemporal_load(x4 + v0 + j * ENC_THREADS);
+#pragma unroll
+        for (int j = 0; j < ENC_PER; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) most = max(most, __float_as_uint(v[j][e]));
+        uint32_t o[ENC_PER];
+        if (sl != 0.f && !__any(most >= ENC_LIMIT)) {
+#pragma unroll
+            for (int j = 0; j < ENC_PER; ++j) o[j] = encode4_plain(v[j], sl);
+        } else {
+#pragma unroll
+            for (int j = 0; j < ENC_PER; ++j)
+                o[j] = encode4(make_float4(v[j][0], v[j][1], v[j][2], v[j][3]), s);
+        }
+#pragma unroll
+        for (int j = 0; j < ENC_PER; ++j) c4[v0 + j * ENC_THREADS] = o[j];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0)
-        for (int64_t i = n16 * 16; i < n; ++i)
+    if (blockIdx.x == gridDim.x - 1)
+        for (int64_t i = tiles * ENC_TILE + t; i < n; i += ENC_THREADS)
             codes[i] = (uint8_t)(e4m3_pair(log1p_fast(x[i]) * s, 0.f) & 0xffu);
 }
 
@@ -134,10 +187,12 @@ hipError_t launch_fp8_encode(const float *x, int64_t n, float in_scale, uint8_t 
                              hipStream_t st)
 {
     if (n == 0) return hipSuccess;
-    const int64_t groups = std::max<int64_t>(1, n / 16);
-    const int64_t blocks = std::min<int64_t>((groups + 255) / 256, 8192);
-    hipLaunchKernelGGL(k_fp8_encode, dim3((unsigned)blocks), dim3(256), 0, st, x, n, in_scale,
-                       codes);
+    const int64_t blocks = std::min<int64_t>(std::max<int64_t>(1, n / ENC_TILE), 1 << 30);
+    // 0: the short form does not hold for this scale (its codes of tiny values
+    // would differ, or its products underflow)
+    const float sl = in_scale >= 0x1p-40f && in_scale <= 0x1p13f ? 0.6931471805599453f * in_scale : 0.f;
+    hipLaunchKernelGGL(k_fp8_encode, dim3((unsigned)blocks), dim3(ENC_THREADS), 0, st, x, n,
+                       in_scale, sl, codes);
     return hipGetLastError();
 }
 
