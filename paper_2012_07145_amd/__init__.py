@@ -13,6 +13,7 @@ import numpy as np
 
 from . import _lib
 from ._lib import REQUEST_DTYPE as _REQUEST_DTYPE
+from ._lib import RESULT_DTYPE as _RESULT_DTYPE
 from ._lib import (CM_BF16, CM_FP8, CM_FP32, CM_MAX_K, CM_N_PARAMS, CM_STAGE_CHUNK,  # noqa: F401
                    CmError, check, lib)
 
@@ -466,15 +467,21 @@ class Server:
         in ticket order (each the request's beam)."""
         t = np.ascontiguousarray(tickets, dtype=np.uint64)
         n = len(t)
-        outs = (_lib.cm_result * max(n, 1))()
-        bufs = []
-        for j in range(n):
-            res, idx, val = self._result(self.k)
-            outs[j] = res
-            bufs.append((idx, val))
+        # one array of each kind for all beams, pointed into by numpy in one
+        # pass per field: a ctypes object and two arrays per ticket cost 4 us
+        # each, 1 ms for the 256 requests of a serving step whose device time
+        # is 0.3 ms
+        idx = np.empty((max(n, 1), self.k), np.int32)
+        val = np.empty((max(n, 1), self.k), np.float32)
+        outs = np.zeros(max(n, 1), _RESULT_DTYPE)
+        outs["k"] = self.k
+        at = np.arange(max(n, 1), dtype=np.uint64) * np.uint64(4 * self.k)
+        outs["idx"] = np.uint64(idx.ctypes.data) + at
+        outs["val"] = np.uint64(val.ctypes.data) + at
         check(lib().cm_serve_wait_all(self.handle, n, t.ctypes.data_as(ctypes.c_void_p),
-                                      int(timeout_ms), outs))
-        return [(idx[:outs[j].n], val[:outs[j].n]) for j, (idx, val) in enumerate(bufs)]
+                                      int(timeout_ms),
+                                      outs.ctypes.data_as(ctypes.POINTER(_lib.cm_result))))
+        return [(i[:m], v[:m]) for i, v, m in zip(idx, val, outs["n"][:n].tolist())]
 
     def stats(self) -> dict:
         s = _lib.cm_server_stats()

@@ -108,6 +108,14 @@ class cm_result(ctypes.Structure):
                 ("t_done_us", ctypes.c_double)]
 
 
+# As a numpy record, for pointing every result of a batch into one array.
+RESULT_DTYPE = np.dtype({"names": ["k", "n", "idx", "val"],
+                         "formats": [np.int32, np.int32, np.uint64, np.uint64],
+                         "offsets": [cm_result.k.offset, cm_result.n.offset,
+                                     cm_result.idx.offset, cm_result.val.offset],
+                         "itemsize": ctypes.sizeof(cm_result)})
+
+
 class cm_server_stats(ctypes.Structure):
     _fields_ = [("submitted", ctypes.c_int64), ("completed", ctypes.c_int64),
                 ("canceled", ctypes.c_int64), ("candidates", ctypes.c_int64),
