@@ -222,9 +222,9 @@ static_assert(sizeof(StepHead) == 32, "step head layout");
 // Control words of a step, zero between steps (the step kernel leaves them
 // zero when it ends): task queue head, exit count, per-query and per-tile
 // arrival counts.
-// CTL_CLK: running (first start, last end) of the launch's workgroups and
-// CTL_CLKOUT: the last finished launch's pair, as 64-bit words of the
-// constant-rate real-time counter (100 MHz).
+// CTL_CLK: running first start of the launch's workgroups (all ones between
+// steps) and CTL_CLKOUT: the last finished launch's (first start, last end), as
+// 64-bit words of the constant-rate real-time counter (100 MHz).
 constexpr int CTL_NEXT = 0;
 constexpr int CTL_CLK = 16;
 constexpr int CTL_CLKOUT = 24;

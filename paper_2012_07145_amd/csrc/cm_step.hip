@@ -486,9 +486,9 @@ cm_status cm_step_create(const cm_model *model, cm_precision prec, const cm_step
             return fail(CM_ENOMEM, "step allocation failed");
         }
         std::memset(sl.h_block, 0, S->block_bytes);
-        const uint64_t clk_init[2] = {~0ull, 0ull};  // (first start, last end)
+        const uint64_t clk_init = ~0ull;  // no start yet
         if (hipMemset(sl.d_ctl, 0, ctl_words(*S) * sizeof(uint32_t)) != hipSuccess ||
-            hipMemcpy(sl.d_ctl + CTL_CLK, clk_init, sizeof clk_init, hipMemcpyHostToDevice) !=
+            hipMemcpy(sl.d_ctl + CTL_CLK, &clk_init, sizeof clk_init, hipMemcpyHostToDevice) !=
                 hipSuccess) {
             free_step(S);
             return fail(CM_EDEVICE, "step initialisation failed");

@@ -131,15 +131,18 @@ __device__ __forceinline__ void step_body(const StepHead *__restrict__ h,
     uint32_t *tcnt = ctl + CTL_TCNT;
     unsigned long long *clk = reinterpret_cast<unsigned long long *>(ctl + CTL_CLK);
 
+    // A workgroup's first task is its own number, and one without a task leaves
+    // at once: a word that every workgroup of the grid adds to costs each of
+    // them the others' additions (512 of them made an add and its return 4 to 5
+    // us of a lone small query's 30).
+    const int ngroups = min((int)gridDim.x, ntasks);
+    int t = blockIdx.x;
+    if (t >= ngroups) return;
     for (int j = tid; j < nq; j += NT) task0[j] = qs[j].task0;
     if constexpr (LogTable<Pack>::n > 1) load_table(tab, pk);
-    if (tid == 0) {
-        atomicMin(&clk[0], (unsigned long long)__builtin_amdgcn_s_memrealtime());
-        s_next = (int)atomicAdd(&ctl[CTL_NEXT], 1u);
-    }
+    if (tid == 0) atomicMin(&clk[0], (unsigned long long)__builtin_amdgcn_s_memrealtime());
     const Pairs kp = make_pairs();
     __syncthreads();
-    int t = s_next;
     while (t < ntasks) {
         // the query of task t: the last q with task0[q] <= t
         int lo = 0, hi = nq - 1;
@@ -162,14 +165,17 @@ __device__ __forceinline__ void step_body(const StepHead *__restrict__ h,
         __syncthreads();
         if (tid == 0) {
             const uint32_t need = (uint32_t)min(tpt, D.ntasks - tile * tpt);
-            const uint32_t next = atomicAdd(&ctl[CTL_NEXT], 1u);
-            const uint32_t arrived = atomicAdd(&tcnt[D.tile0 + tile], 1u);
+            // the queue past the first tasks, while it holds any; a tile of one
+            // task has no other workgroup to wait for
+            uint32_t next = (uint32_t)ntasks, arrived = 0;
+            if (ntasks > ngroups) next = (uint32_t)ngroups + atomicAdd(&ctl[CTL_NEXT], 1u);
+            if (need > 1) arrived = atomicAdd(&tcnt[D.tile0 + tile], 1u);
             s_next = (int)next;
             s_tail = arrived == need - 1;
+            if (need > 1 && arrived == need - 1) atomicExch(&tcnt[D.tile0 + tile], 0u);
         }
         __syncthreads();
         if (s_tail) {
-            if (tid == 0) atomicExch(&tcnt[D.tile0 + tile], 0u);
             select_tile(D, q, tile, k, qcnt, tpart, tsh, s_query_last);
         }
         t = s_next;
@@ -177,14 +183,13 @@ __device__ __forceinline__ void step_body(const StepHead *__restrict__ h,
     }
     // the last workgroup to leave resets the queue for the next launch (every
     // other workgroup has made its final queue fetch before counting itself)
-    // and publishes the launch's clock pair
+    // and publishes the launch's clock pair: its own leaving is the launch's
+    // end, so that no workgroup waits for a maximum in memory
     if (tid == 0) {
-        atomicMax(&clk[1], (unsigned long long)__builtin_amdgcn_s_memrealtime());
-        wait_stores();
-        if (atomicAdd(&ctl[CTL_DONE], 1u) == gridDim.x - 1) {
+        if (atomicAdd(&ctl[CTL_DONE], 1u) == (uint32_t)ngroups - 1) {
             unsigned long long *out = reinterpret_cast<unsigned long long *>(ctl + CTL_CLKOUT);
             const unsigned long long c0 = atomicExch(&clk[0], ~0ull);
-            const unsigned long long c1 = atomicExch(&clk[1], 0ull);
+            const unsigned long long c1 = __builtin_amdgcn_s_memrealtime();
             store_shared(&out[0], c0);
             store_shared(&out[1], c1);
             if (h->clk_out) {
