@@ -289,12 +289,20 @@ struct Weights {
     float b2v[4];
 };
 
-// Refill this wave's LDS slice with the hoisted rows of stages s .. s+n-1.
-// Only this wave reads its slice and its LDS operations complete in order.
+// Refill this wave's LDS slice with the hoisted rows of stages s .. s+n-1
+// (1 <= n <= USTAGE; entries past them get copies of the last).  Only this
+// wave reads its slice and its LDS operations complete in order.  The rows are
+// global memory (the pointer may come from a descriptor in memory): a flat
+// load would also count as an LDS operation, and every later wait for a load
+// would then wait for all of them.
 __device__ inline void refill_u(float4 *ur, const float4 *ug, int s, int n, int lane)
 {
-    const int nv = n * (H / 4);
-    for (int v = lane; v < nv; v += 64) ur[v] = ug[(int64_t)s * (H / 4) + v];
+    static_assert(USTAGE * H / 4 == 128, "two 16-byte entries per lane");
+    const auto *g = (const __attribute__((address_space(1))) f32x4 *)(ug + (int64_t)s * (H / 4));
+    const int last = n * (H / 4) - 1;
+    const f32x4 a = g[min(lane, last)], b = g[min(lane + 64, last)];
+    ur[lane] = __builtin_bit_cast(float4, a);
+    ur[lane + 64] = __builtin_bit_cast(float4, b);
     __builtin_amdgcn_wave_barrier();
 }
 

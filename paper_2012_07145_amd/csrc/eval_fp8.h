@@ -87,13 +87,15 @@ struct StageIn8 {
     bool bad;     // memoized rows: the stage's row number is outside the table
 };
 
+// TP: cache policy of the terms.
+template <int TP>
 __device__ inline void load_stage8(StageIn8 &in, __amdgpu_buffer_rsrc_t xr,
                                    __amdgpu_buffer_rsrc_t tr, uint32_t xsoff, uint32_t tsoff,
                                    uint32_t xo, uint32_t to)
 {
     in.x0 = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(xr, xo, xsoff, 0));
     in.x1 = __builtin_amdgcn_raw_buffer_load_b32(xr, xo + 16, xsoff, 0);
-    in.t = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(tr, to, tsoff, 0));
+    in.t = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(tr, to, tsoff, TP));
 }
 
 __device__ __forceinline__ float stage_math8(const StageIn8 &in, const float4 *us, int hf,
@@ -171,7 +173,8 @@ __device__ __forceinline__ void eval_group8(const QueryView8 &Q, int group, int 
     const uint32_t tstep = (uint32_t)Q.N * C * 4;
     const uint32_t xbytes = kIndexed ? Q.rows * FS : xstep * (uint32_t)Q.S;
     const __amdgpu_buffer_rsrc_t xr = buffer_over(Q.x, xbytes);
-    const __amdgpu_buffer_rsrc_t tr = buffer_over(Q.t, tstep * (uint32_t)Q.S);
+    const uint32_t tbytes = tstep * (uint32_t)Q.S;
+    const __amdgpu_buffer_rsrc_t tr = buffer_over(Q.t, tbytes);
     uint32_t xsoff = (uint32_t)s0 * xstep;
     uint32_t tsoff = (uint32_t)s0 * tstep;
     uint32_t xo = (uint32_t)ic * FS + hf * 20;  // code bytes 20*hf .. +20
@@ -190,13 +193,69 @@ __device__ __forceinline__ void eval_group8(const QueryView8 &Q, int group, int 
     float4 *ur = sh.u[wave];
 
     float sum = 0.f, comp = 0.f;
-    if (s0 < s1) {
+    if (!kStage && !kIndexed && s0 < s1) {
+        // Three register buffers in turn: a stage's loads are issued two stages
+        // ahead of its arithmetic, which is short (two matrix instructions),
+        // so that each wave keeps two stages of 2.3 KB in flight.  They are
+        // issued without a branch -- past the last stage at an offset outside
+        // the buffers, which reads nothing -- because the compiler can count
+        // the loads in flight, and wait for the oldest only, where every path
+        // issues the same ones.  The terms are non-temporal (whole lines, read
+        // once); the codes are not, since two loads share each of their lines.
+        // 128 queries through the persistent step: 147 us with two buffers, 140
+        // us so, 135 us with the terms' policy (147 with the codes' too); 64 x
+        // 32,768 per call 46, 45 and 39 us.
+        StageIn8 in[3];
+        int ahead = s0;  // the stage loaded next
+        auto load_next = [&](StageIn8 &stage) {
+            const bool any = ahead < s1;  // uniform
+            load_stage8<bf16eval::STREAM>(stage, xr, tr, xsoff, tsoff, any ? xo : xbytes,
+                                          any ? to : tbytes);
+            stage.bad = false;
+            ++ahead;
+            xsoff += ahead < s1 ? xstep : 0u;
+            tsoff += ahead < s1 ? tstep : 0u;
+        };
+        // hoisted rows are staged U8 stages at a time, outside the loop: a
+        // branch in it with loads of its own would end the count
+        constexpr int U8 = USTAGE / 3 * 3;
+        for (int c0 = s0; c0 < s1; c0 += U8) {
+            const int c1 = min(c0 + U8, s1);
+            refill_u(ur, ug, c0, c1 - c0, lane);
+            auto stage = [&](const StageIn8 &x, int s) {
+                stage_math8(x, ur + (s - c0) * (H / 4), hf, w, sum, comp);
+            };
+            if (c0 == s0) {
+                load_next(in[0]);
+                asm volatile("" ::: "memory");
+                load_next(in[1]);
+            }
+            int s = c0;
+            for (; s + 3 <= c1; s += 3) {
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {
+                    load_next(in[(j + 2) % 3]);
+                    // keep the loads here, ahead of their use
+                    asm volatile("" ::: "memory");
+                    stage(in[j], s + j);
+                }
+            }
+            // the last chunk's remainder (others are whole threes)
+            if (s < c1) stage(in[0], s);
+            if (s + 1 < c1) stage(in[1], s + 1);
+        }
+    }
+    if ((kStage || kIndexed) && s0 < s1) {
+        // Per-stage costs and memoized rows keep two buffers and cached terms:
+        // the form above took 32 instead of 30 us for 5 queries' stage costs
+        // (a store in its loop) and 47 instead of 42 us for 17 queries' rows
+        // (bound by the lines that the L2s fetch, not by latency).
         StageIn8 A, B;
         if (kIndexed) {
             point_at(row_of(s0));
             if (s0 + 1 < s1) rnext = row_of(s0 + 1);
         }
-        load_stage8(A, xr, tr, xsoff, tsoff, xo, to);
+        load_stage8<0>(A, xr, tr, xsoff, tsoff, xo, to);
         A.bad = bad;
         for (int s = s0; s < s1; s += 2) {
             if ((s - s0) % USTAGE == 0) refill_u(ur, ug, s, min(USTAGE, s1 - s), lane);
@@ -208,7 +267,7 @@ __device__ __forceinline__ void eval_group8(const QueryView8 &Q, int group, int 
                     if (s + 2 < s1) rnext = row_of(s + 2);
                 }
             }
-            load_stage8(B, xr, tr, xsoff, tsoff, xo, to);
+            load_stage8<0>(B, xr, tr, xsoff, tsoff, xo, to);
             B.bad = bad;
             asm volatile("" ::: "memory");
             const float va = stage_math8(A, ur + ((s - s0) % USTAGE) * (H / 4), hf, w, sum, comp);
@@ -224,7 +283,7 @@ __device__ __forceinline__ void eval_group8(const QueryView8 &Q, int group, int 
                     if (s + 3 < s1) rnext = row_of(s + 3);
                 }
             }
-            load_stage8(A, xr, tr, xsoff, tsoff, xo, to);
+            load_stage8<0>(A, xr, tr, xsoff, tsoff, xo, to);
             A.bad = bad;
             asm volatile("" ::: "memory");
             const float vb =
