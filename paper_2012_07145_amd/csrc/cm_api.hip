@@ -728,13 +728,12 @@ cm_status cm_penalize_known_bad(const cm_batch *b, const uint64_t *hashes,
         PenaltyLaunch L;
         std::memset(&L, 0, sizeof L);
         L.nq = ng;
-        int64_t c0 = 0;
         for (int32_t j = 0; j < ng; ++j) {
             const cm_query &Q = b->queries[g0 + j];
             L.q[j].N = Q.n_cands;
             L.q[j].cost_off = Q.cost_off;
-            L.q[j].cand0 = c0;
-            c0 += Q.n_cands;
+            L.q[j].block0 = L.blocks;
+            L.blocks += (int32_t)cdiv(Q.n_cands, PENALTY_THREADS);
         }
         CM_HIP(launch_penalty(L, hashes, bad_sorted, n_bad, penalty, cost, s));
     }
@@ -820,10 +819,10 @@ cm_status cm_topk_per_query(const float *cost, const cm_batch *b, int32_t k, cm_
             t.cost_off = Q.cost_off;
             t.tile0 = (int32_t)tile;
             t.ntiles = (int32_t)std::max<int64_t>(1, cdiv(Q.n_cands, TOPK_CALL_TILE));
-            L.max_tiles = std::max(L.max_tiles, t.ntiles);
             tile += t.ntiles;
         }
         if (tile * k > w.tpart_cap) return fail(CM_E2BIG, "batch exceeds workspace beam lists");
+        L.ntasks = (int32_t)tile;
         CM_HIP(launch_topk(L, cost, w.d_tpart, w.d_tcnt, idx_out, val_out, s));
     }
     return CM_OK;

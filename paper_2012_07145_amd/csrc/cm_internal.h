@@ -150,16 +150,17 @@ struct FreezeLaunch {
     FreezeQ q[QMAX];
 };
 
+constexpr int PENALTY_THREADS = 256;  // candidates per workgroup
+
 struct PenaltyQ {
     int32_t N;
-    int32_t pad;
+    int32_t block0;    // first workgroup of the query
     int64_t cost_off;  // costs (and hashes) of the query
-    int64_t cand0;     // candidates of the launch's earlier queries
 };
 
 struct PenaltyLaunch {
     int32_t nq;
-    int32_t pad;
+    int32_t blocks;
     PenaltyQ q[QMAX];
 };
 
@@ -173,7 +174,7 @@ struct TopkQ {
 
 struct TopkLaunch {
     int32_t nq;
-    int32_t max_tiles; // most tiles of a query
+    int32_t ntasks;    // tiles
     int32_t k;
     int32_t pad;
     TopkQ q[QMAX];
@@ -315,6 +316,20 @@ __device__ inline T load_shared(const T *p)
 }
 // Wait until this wave's stores have completed.
 __device__ inline void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+// The last of a launch's n <= 64 queries whose start, start_of(j) (ascending
+// from 0), is at or before t (uniform): one load per lane and a vote.  A walk
+// over the descriptors waits for a scalar load per query: 7.5 us instead of
+// 4.2 us for the hoist of 17 queries, 37 instead of 34 us for the evaluation
+// of their memoized rows.
+template <class Start>
+__device__ inline int query_at(int n, int t, Start start_of)
+{
+    if (n == 1) return 0;
+    const int lane = (int)threadIdx.x & 63;
+    const bool at = start_of(min(lane, n - 1)) <= t && lane < n;
+    return __builtin_amdgcn_readfirstlane(__popcll(__ballot(at)) - 1);
+}
 
 // Host side: record a thread-local error message and return `st`.
 cm_status fail(cm_status st, const char *fmt, ...) __attribute__((format(printf, 2, 3)));

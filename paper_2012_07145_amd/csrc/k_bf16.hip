@@ -9,14 +9,6 @@ namespace {
 
 using namespace bf16eval;
 
-__device__ inline int find_task_query(const EvalLaunch &L, int t)
-{
-    int q = 0;
-    for (int j = 1; j < L.nq; ++j)
-        if (L.q[j].task0 <= t) q = j;
-    return q;
-}
-
 template <bool kStage, bool kIndexed>
 __global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_eval_bf16(
     EvalLaunch L, const Bf16Pack *__restrict__ pk, const uint16_t *sched, const float *terms,
@@ -29,7 +21,7 @@ __global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu
     const int lane = threadIdx.x & 63;
     // wave-uniform values are kept in scalar registers
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int q = find_task_query(L, blockIdx.x);
+    const int q = query_at(L.nq, blockIdx.x, [&](int j) { return L.q[j].task0; });
     const EvalQ &E = L.q[q];
     QueryView Q;
     // memoized rows: sched is the row table and sched_off locates the row numbers

@@ -11,14 +11,6 @@ namespace {
 
 using namespace fp8eval;
 
-__device__ inline int find_task_query(const EvalLaunch &L, int t)
-{
-    int q = 0;
-    for (int j = 1; j < L.nq; ++j)
-        if (L.q[j].task0 <= t) q = j;
-    return q;
-}
-
 template <bool kStage, bool kIndexed>
 __global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_eval_fp8(
     EvalLaunch L, const Fp8Pack *__restrict__ pk, const uint8_t *codes, const float *terms,
@@ -28,7 +20,7 @@ __global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu
     __shared__ bf16eval::GroupShared sh;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int q = find_task_query(L, blockIdx.x);
+    const int q = query_at(L.nq, blockIdx.x, [&](int j) { return L.q[j].task0; });
     const EvalQ &E = L.q[q];
     QueryView8 Q;
     // memoized rows: codes is the row table and sched_off locates the row numbers

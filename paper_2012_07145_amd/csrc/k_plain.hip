@@ -19,17 +19,6 @@
 namespace cm {
 namespace {
 
-__device__ inline int find_query(const EvalLaunch &L, int t, bool by_stage)
-{
-    // Largest q with start(q) <= t.  Uniform across the workgroup.
-    int q = 0;
-    for (int j = 1; j < L.nq; ++j) {
-        int start = by_stage ? L.q[j].hrow0 : L.q[j].task0;
-        if (start <= t) q = j;
-    }
-    return q;
-}
-
 // One stage row of the hoist by a 64-thread workgroup: p = the stage's 56
 // algorithm features, u = its 32 output floats.
 __device__ inline void hoist_row(const float *__restrict__ params, const float *__restrict__ beta,
@@ -63,7 +52,7 @@ __global__ __launch_bounds__(64) void k_hoist(EvalLaunch L, const float *__restr
 {
     __shared__ float lp[FP];
     __shared__ float ep[E];
-    const int q = find_query(L, blockIdx.x, true);
+    const int q = query_at(L.nq, blockIdx.x, [&](int j) { return L.q[j].hrow0; });
     const int s = blockIdx.x - L.q[q].hrow0;
     hoist_row(params, beta, fold, scale, pipe + L.q[q].pipe_off + (int64_t)s * FP,
               U + L.q[q].u_off + (int64_t)s * H, lp, ep);
@@ -291,7 +280,7 @@ k_eval_fp32(EvalLaunch L, const Fp32Pack *__restrict__ pk, const float *sched, c
     const float *xw = reinterpret_cast<const float *>(xsw);
     int round = 0;
     for (int task = blockIdx.x; task < L.ntasks; task += gridDim.x) {
-        const int q = find_query(L, task, false);
+        const int q = query_at(L.nq, task, [&](int j) { return L.q[j].task0; });
         const EvalQ &Q = L.q[q];
         const int i0 = (task - Q.task0) * FP32_TILE;
         const int rows = min(FP32_TILE, Q.N - i0);

@@ -1,6 +1,6 @@
 // k_topk.hip -- per-query beam selection kernel (Sec. 4, Sec. 4.4): one
-// workgroup per tile of a query's candidates (grid: tiles x queries), query
-// descriptors passed by value; the selection itself is in topk_dev.h.
+// workgroup per tile of a query's candidates, query descriptors passed by
+// value; the selection itself is in topk_dev.h.
 #include "topk_dev.h"
 
 namespace cm {
@@ -25,9 +25,9 @@ __global__ __launch_bounds__(NT) void k_topk(TopkLaunch L, const float *__restri
     __shared__ TopkShared<NT> sh;
     __shared__ int last;
     const int t = threadIdx.x;
-    const int q = blockIdx.y, tile = blockIdx.x;
+    const int q = query_at(L.nq, blockIdx.x, [&](int j) { return L.q[j].tile0; });
     const TopkQ &Q = L.q[q];
-    if (tile >= Q.ntiles) return;
+    const int tile = (int)blockIdx.x - Q.tile0;
     const int k = L.k;
     const float *c = cost + Q.cost_off;
 
@@ -56,8 +56,8 @@ __global__ __launch_bounds__(NT) void k_topk(TopkLaunch L, const float *__restri
 hipError_t launch_topk(const TopkLaunch &L, const float *cost, uint64_t *tpart, int32_t *tcnt,
                        int32_t *idx_out, float *val_out, hipStream_t st)
 {
-    if (L.nq == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_topk, dim3(L.max_tiles, L.nq), dim3(NT), 0, st, L, cost, tpart, tcnt,
+    if (L.ntasks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_topk, dim3(L.ntasks), dim3(NT), 0, st, L, cost, tpart, tcnt,
                        idx_out, val_out);
     return hipGetLastError();
 }
