@@ -109,16 +109,28 @@ __device__ inline uint32_t key_bound(int B, int r)
     return (uint32_t)((float)(2 * r + 16) * (4294967040.f / (float)B));
 }
 
-__global__ __launch_bounds__(ST) void k_s_insert(const SampleQ *__restrict__ q, int nq,
+// Descriptors of a call of at most VALUE_Q queries, passed to the first kernel
+// by value; it leaves them in memory for the others.  Larger calls copy them
+// from pinned memory ahead of it, which costs a copy, the event that guards
+// the pinned block and the gaps around them: 5 us a call.
+constexpr int VALUE_Q = 64;
+struct SampleArgs {
+    SampleQ q[VALUE_Q];
+};
+
+template <bool kByValue>
+__global__ __launch_bounds__(ST) void k_s_insert(SampleArgs args, SampleQ *__restrict__ dq, int nq,
                                                  const uint64_t *__restrict__ hashes, Table tb,
                                                  uint32_t *__restrict__ slot, uint32_t *arena)
 {
+    const SampleQ *q = kByValue ? args.q : dq;
     __shared__ u64 key[LSLOTS];
     __shared__ uint32_t cnt[LSLOTS + 1];  // members, then the slot in the query's table
     __shared__ uint16_t used[CHUNK + 1];
     __shared__ uint32_t nused;
     const int t = threadIdx.x;
     if (blockIdx.x == 0 && t == 0) *arena = 0;
+    if (kByValue && blockIdx.x == 0 && t < nq) dq[t] = args.q[t];
     const int qi = query_of_chunk(q, nq, blockIdx.x);
     const SampleQ Q = q[qi];
     const uint32_t i0 = (uint32_t)(blockIdx.x - Q.chunk0) * CHUNK;
@@ -572,17 +584,22 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
 
     hipStream_t s = (hipStream_t)stream;
     const int nq = b->n_queries;
-    CM_HIP(hipEventSynchronize(sp->staged));  // the previous call's copy has left h_q
+    const bool by_value = nq <= VALUE_Q;
+    SampleArgs args;
+    SampleQ *const hq = by_value ? args.q : sp->h_q;
+    if (!by_value) CM_HIP(hipEventSynchronize(sp->staged));  // the last copy has left h_q
     int64_t base = 0;
     int32_t chunks = 0;
     for (int q = 0; q < nq; ++q) {
         const cm_query &Q = b->queries[q];
-        sp->h_q[q] = SampleQ{base, Q.cost_off, seeds[q], Q.n_cands, chunks};
+        hq[q] = SampleQ{base, Q.cost_off, seeds[q], Q.n_cands, chunks};
         base += Q.n_cands;
         chunks += std::max(1, (int32_t)(((int64_t)Q.n_cands + CHUNK - 1) / CHUNK));
     }
-    CM_HIP(hipMemcpyAsync(sp->d_q, sp->h_q, sizeof(SampleQ) * nq, hipMemcpyHostToDevice, s));
-    CM_HIP(hipEventRecord(sp->staged, s));
+    if (!by_value) {
+        CM_HIP(hipMemcpyAsync(sp->d_q, hq, sizeof(SampleQ) * nq, hipMemcpyHostToDevice, s));
+        CM_HIP(hipEventRecord(sp->staged, s));
+    }
 
     if (!sp->clean) {  // an earlier call's launches failed
         hipLaunchKernelGGL(k_s_clear, dim3(clear_blocks(sp->slots)), dim3(ST), 0, s, sp->tb,
@@ -591,7 +608,12 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
     }
     sp->clean = false;
     const dim3 g(chunks), t(ST);
-    hipLaunchKernelGGL(k_s_insert, g, t, 0, s, sp->d_q, nq, hashes, sp->tb, sp->slot, sp->arena);
+    if (by_value)
+        hipLaunchKernelGGL(k_s_insert<true>, g, t, 0, s, args, sp->d_q, nq, hashes, sp->tb,
+                           sp->slot, sp->arena);
+    else
+        hipLaunchKernelGGL(k_s_insert<false>, g, t, 0, s, SampleArgs{}, sp->d_q, nq, hashes,
+                           sp->tb, sp->slot, sp->arena);
     CM_HIP(hipGetLastError());
     const int64_t slots = 2 * T + nq;
     hipLaunchKernelGGL(k_s_alloc, dim3((unsigned)((slots + 4 * AT - 1) / (4 * AT))), dim3(AT), 0,
