@@ -237,8 +237,8 @@ cm_status cm_eval_stages(const cm_model *model, cm_precision precision,
  * representatives' indices are written ascending to sel_idx[cost_off + j]
  * (device int32, room for n_cands) and their number to sel_count[q]
  * (device).  seeds is a host array of n_queries seeds.  Asynchronous on
- * `stream` (the descriptors are staged through pinned memory); allocates
- * nothing.  One sampler serves one stream at a time.
+ * `stream` (the descriptors of more than 64 queries are staged through pinned
+ * memory); allocates nothing.  One sampler serves one stream at a time.
  * Errors: CM_EINVAL (NULL pointer, bad descriptor, wrong device), CM_E2BIG
  * (more queries or options than the sampler holds), CM_ENOMEM (create),
  * CM_EDEVICE. */

@@ -56,15 +56,40 @@ def test_sample_bucket_sizes(cm, oracle_mod):
 SHORT = [(256, 3359416), (256, 6203968), (200, 6634266), (512, 29459833)]
 
 
-def test_sample_short_candidate_lists(cm, oracle_mod):
+@pytest.mark.parametrize("others", [0, 300, 3000])  # one chunk (a launch of its own) and several
+def test_sample_short_candidate_lists(cm, oracle_mod, others):
     hashes = [np.full(b, 99, np.uint64) for b, _ in SHORT]
     seeds = np.array([s for _, s in SHORT], np.uint64)
     # the bucket's options come first, so their keys are the search's
     rng = np.random.default_rng(4)
-    hashes = [np.concatenate([h, bucket_hashes(rng, 3000)]) for h in hashes]
+    if others:
+        hashes = [np.concatenate([h, bucket_hashes(rng, others)]) for h in hashes]
     sp = cm.cm_sampler_create(len(hashes), sum(h.size for h in hashes))
     sel, cnt, descs = run(cm, sp, hashes, seeds)
     check(oracle_mod, hashes, seeds, sel, cnt, descs)
+    sp.close()
+
+
+@pytest.mark.parametrize("nq", [1, 64, 65, 130])
+def test_sample_small_queries(cm, oracle_mod, nq):
+    """Every query within one chunk: a single launch, with descriptors by value
+    and from memory; larger queries on the same sampler in between."""
+    rng = np.random.default_rng(nq)
+    sizes = [int(rng.integers(0, 1025)) for _ in range(nq)]
+    sizes[0] = 1024
+    hashes = [bucket_hashes(rng, n) if n else np.zeros(0, np.uint64) for n in sizes]
+    for j in range(0, nq, 3):
+        hashes[j] = rng.integers(0, 5, sizes[j]).astype(np.uint64)
+        hashes[j][:: 7] = FULL
+    seeds = rng.integers(0, 2 ** 64, nq, dtype=np.uint64)
+    sp = cm.cm_sampler_create(nq, max(sum(sizes), 5000))
+    for _ in range(2):
+        sel, cnt, descs = run(cm, sp, hashes, seeds)
+        check(oracle_mod, hashes, seeds, sel, cnt, descs)
+        assert sel[-1] == -5
+        big = [bucket_hashes(rng, 4000)]
+        sel, cnt, descs = run(cm, sp, big, [7])
+        check(oracle_mod, big, [7], sel, cnt, descs)
     sp.close()
 
 
