@@ -59,6 +59,28 @@ namespace {
 
 using cm::fail;
 
+// Table of the float32 evaluator's logarithm, the same for every model.
+struct LogTable {
+    cm::LogEntry e[cm::LOG32_N];
+    LogTable()
+    {
+        // distances from a midpoint of two floats, in units in the last place,
+        // beyond which the logarithm rounds as log1pf does (measured beside
+        // its code), per exponent of 1 + x
+        constexpr double near[] = {0.0800, 0.0342, 0.0173, 0.0091, 0.0091, 0.0091, 0.0042, 0.0042,
+                                   0.0042, 0.0042, 0.0042, 0.0042, 0.0042, 0.0042, 0.0042, 0.0042};
+        static_assert(sizeof(near) / sizeof(near[0]) == cm::LOG32_OCTAVES, "one per octave");
+        constexpr int M = 1 << cm::LOG32_BITS;
+        for (int i = 0; i < cm::LOG32_N; ++i) {
+            const int x = (i / M + 1) % cm::LOG32_OCTAVES, j = i % M;
+            const bool one = x == 0 && j == 0;
+            e[i].inv = one ? 1.f : (float)(1.0 / std::ldexp(1.0 + (j + 0.5) / M, x));
+            e[i].near = 0x80000000u + (uint32_t)std::ldexp(near[x], 32);
+            e[i].log = one ? 0.0 : -std::log((double)e[i].inv);
+        }
+    }
+};
+
 // Scratch of cm_eval_batch_static: the hoisted rows U[stages][32] of one
 // call, in a file-scope device array.  Every device the library runs on
 // holds its own copy until the process ends; calls on one device share it.
@@ -353,6 +375,8 @@ cm_status cm_model_create(const cm_model_desc *d, const float *params, cm_model 
             if (m < C) w[32 + t] = W2[m * H + 4 * t + g];
         for (int v = 0; v < 10; ++v) std::memcpy(&p32.w[v][lane], w + 4 * v, 16);
     }
+    static const LogTable log_table;
+    std::memcpy(p32.log, log_table.e, sizeof(p32.log));
     std::memcpy(p32.bs, bs, E * sizeof(float));
     std::memcpy(p32.b2, params + OFF_B2, C * sizeof(float));
 

@@ -65,6 +65,18 @@ struct Bf16Pack {
 };
 static_assert(offsetof(Bf16Pack, logtab) % 16 == 0, "table copied in 16-byte units");
 
+// Interval of the float32 evaluator's logarithm: entry (exponent + 15) % 16 of
+// u = 1 + x, then the top LOG32_BITS of its significand, which is where u's
+// bits stand as an index.
+struct alignas(16) LogEntry {
+    float inv;      // 1 / c, c the middle of the interval; 1 for the one that begins at 1
+    uint32_t near;  // 2^31 + width around a midpoint, in units of 2^-32 of a float32's last place
+    double log;     // -log(inv)
+};
+constexpr int LOG32_BITS = 6;
+constexpr int LOG32_OCTAVES = 16;  // x + 1 < 2^16
+constexpr int LOG32_N = LOG32_OCTAVES << LOG32_BITS;
+
 // Operands of the float32 evaluator's three layers, laid out as the 16x16x4
 // float32 matrix core reads them: value v of lane l is row l % 16, term
 // 4t + l / 16 of a step t.  Values 0..19: W_s rows 0..15 (10 steps), then
@@ -74,6 +86,7 @@ struct Fp32Pack {
     float4 w[10][64];
     float4 bs[8];  // b_s, zeros past 24
     float4 b2[4];  // b_2, zeros past 8
+    LogEntry log[LOG32_N];
 };
 
 // e4m3 operands of the FP8 form, laid out as the 32x32x64 fp8 matrix core

@@ -100,35 +100,25 @@ __global__ __launch_bounds__(64) void k_hoist_step(const StepHead *__restrict__ 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 
-// Packed layer operands held by a lane for the whole launch (lane l: row
-// l % 16, term 4t + l / 16 of step t) and its part of the accumulator seeds
-// (rows 4 (l / 16) .. +3).
+// Packed operands of the first layer held by a lane for the whole launch (lane
+// l: row l % 16, term 4t + l / 16 of step t) and its part of the accumulator
+// seeds (rows 4 (l / 16) .. +3).  The other two layers' operands are read from
+// LDS in each stage, where the logarithms need the registers.
 struct Fp32Weights {
-    float ws[2][10], w1[2][6], w2[8];
+    float ws[2][10];
     f32x4 bs[2], b2;
 };
 
 __device__ inline Fp32Weights load_fp32(const Fp32Pack *__restrict__ pk, int lane)
 {
-    float w[40];
-#pragma unroll
-    for (int v = 0; v < 10; ++v) {
-        const float4 x = pk->w[v][lane];
-        w[4 * v] = x.x;
-        w[4 * v + 1] = x.y;
-        w[4 * v + 2] = x.z;
-        w[4 * v + 3] = x.w;
-    }
     Fp32Weights W;
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
+    for (int v = 0; v < 5; ++v) {
+        const float4 x = pk->w[v][lane];
+        const float w[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-        for (int t = 0; t < 10; ++t) W.ws[hh][t] = w[10 * hh + t];
-#pragma unroll
-        for (int t = 0; t < 6; ++t) W.w1[hh][t] = w[20 + 6 * hh + t];
+        for (int j = 0; j < 4; ++j) W.ws[(4 * v + j) / 10][(4 * v + j) % 10] = w[j];
     }
-#pragma unroll
-    for (int t = 0; t < 8; ++t) W.w2[t] = w[32 + t];
     const int g = lane >> 4;
     const float4 s0 = pk->bs[g], s1 = pk->bs[4 + g], s2 = pk->b2[g];
     W.bs[0] = f32x4{s0.x, s0.y, s0.z, s0.w};
@@ -178,19 +168,104 @@ __device__ inline __amdgpu_buffer_rsrc_t rows_at(const float *p, int bytes)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(p), (short)0, bytes, 0x00020000);
 }
 
-// One stage of 16 candidates: x = the raw features 4t + g of candidate
+// log1p(x) in float64, rounded to float32, and whether that may not be
+// log1pf(x) (`unsure`).  With u = 1 + x in an interval of middle c and
+// 1/c = inv rounded to float32, log(u) = -log(inv) + log1p(r) for
+// r = x inv + (inv - 1), |r| < 2^-6.9, by five terms; in the interval at 1,
+// inv = 1 and r = x, which keeps small x and 0 exact.  log1pf rounds to the
+// other neighbour only where the value lies within its own error of the
+// midpoint of two floats: over every float32 from 0 to 65,535 at most 0.0787,
+// 0.0336, 0.0170, 0.0089 units in the last place for u of exponent 0, 1, 2,
+// 3 .. 5 and 0.0041 above.  A value nearer to a midpoint than its entry's width
+// (a little more) and any other x (negative, -0, larger, NaN) is left to
+// log1pf, so that every result has its bits.
+constexpr uint32_t LOG32_END = 0x477fff00u;  // 65,535
+
+__device__ inline float log1p64(float x, const LogEntry &T, uint64_t &near, uint64_t &outside)
+{
+    const double inv = (double)T.inv;
+    const double r = fma((double)x, inv, inv - 1.0);
+    const double p = fma(r, fma(r, fma(r, 0.2, -0.25), 1.0 / 3.0), -0.5);
+    const double y = fma(r * r, p, r) + T.log;
+    // the 29 bits that float32 drops, as a distance from one half of its unit
+    const uint32_t low = ((uint32_t)__builtin_bit_cast(uint64_t, y) << 3) + T.near;
+    near = __builtin_amdgcn_ballot_w64(low <= 2 * T.near);  // 2^32 drops out of both
+    outside = __builtin_amdgcn_ballot_w64(__float_as_uint(x) >= LOG32_END);
+    return (float)y;
+}
+
+// log1pf of a wave's 10 values per lane: those that are not sure (2 to 3% of
+// lognormal features) are gathered in the wave's list and go through log1pf
+// 64 at a time.  Five table reads are in flight together, and a sure value's
+// write to the list and its read go to a slot of its lane behind the list, so
+// that there is no branch between them.
+constexpr int LIST32 = 64 * 10;
+__device__ __forceinline__ void log1p_wave(float (&x)[10], const LogEntry *tab, float *list)
+{
+    const int lane = threadIdx.x & 63;
+    uint64_t mask[10];
+    uint32_t slot[10];
+    uint32_t n = 0;
+#pragma unroll
+    for (int half = 0; half < 10; half += 5) {
+        LogEntry T[5];
+#pragma unroll
+        for (int t = 0; t < 5; ++t)
+            T[t] = tab[(__float_as_uint(1.f + x[half + t]) >> (23 - LOG32_BITS)) & (LOG32_N - 1)];
+#pragma unroll
+        for (int t = half; t < half + 5; ++t) {
+            uint64_t near, outside;
+            const float y = log1p64(x[t], T[t - half], near, outside);
+            const uint64_t m = near | outside;
+            const uint32_t at = __builtin_amdgcn_mbcnt_hi(
+                (uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, n));
+            slot[t] = __builtin_amdgcn_inverse_ballot_w64(m) ? at : (uint32_t)(LIST32 + lane);
+            list[slot[t]] = x[t];
+            n += (uint32_t)__popcll(m);
+            mask[t] = m;
+            x[t] = y;
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t j = lane; j < n; j += 64) list[j] = log1pf(list[j]);
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int half = 0; half < 10; half += 5) {
+        float y[5];
+#pragma unroll
+        for (int t = 0; t < 5; ++t) y[t] = list[slot[half + t]];
+        asm volatile("" : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3]), "+v"(y[4]));
+#pragma unroll
+        for (int t = 0; t < 5; ++t)
+            x[half + t] = __builtin_amdgcn_inverse_ballot_w64(mask[half + t]) ? y[t] : x[half + t];
+    }
+}
+
+// One stage of 16 candidates: x = log1p of features 4t + g of candidate
 // lane % 16, u = the stage's hoisted units 4g .. +3 and 16 + 4g .. +3, tr =
 // cost terms 4g .. 4g+3 of that candidate (g < 2).  Returns the stage's cost
 // in lanes 16..31.
 __device__ __forceinline__ float stage32(const float (&x)[10], const f32x4 (&u)[2], const f32x4 &tr,
-                                         const Fp32Weights &W)
+                                         const Fp32Weights &W, const float4 (*wt)[64])
 {
+    const int lane = threadIdx.x & 63;
+    float wl[20];  // W_1 (12) and W_2 (8)
+#pragma unroll
+    for (int v = 0; v < 5; ++v) {
+        const float4 q = wt[v][lane];
+        wl[4 * v] = q.x;
+        wl[4 * v + 1] = q.y;
+        wl[4 * v + 2] = q.z;
+        wl[4 * v + 3] = q.w;
+    }
+    // matrix instructions first: the other waves' logarithms fill the cycles
+    // between them (2% at 64 x 32,768)
+    __builtin_amdgcn_s_setprio(1);
     f32x4 e0 = W.bs[0], e1 = W.bs[1];
 #pragma unroll
     for (int t = 0; t < 10; ++t) {
-        const float l = log1pf(x[t]);
-        e0 = mfma4(W.ws[0][t], l, e0);
-        e1 = mfma4(W.ws[1][t], l, e1);
+        e0 = mfma4(W.ws[0][t], x[t], e0);
+        e1 = mfma4(W.ws[1][t], x[t], e1);
     }
     transpose4(e0);
     transpose4(e1);
@@ -198,8 +273,8 @@ __device__ __forceinline__ float stage32(const float (&x)[10], const f32x4 (&u)[
 #pragma unroll
     for (int t = 0; t < 6; ++t) {
         const float e = t < 4 ? e0[t] : e1[t - 4];
-        h0 = mfma4(W.w1[0][t], e, h0);
-        h1 = mfma4(W.w1[1][t], e, h1);
+        h0 = mfma4(wl[t], e, h0);
+        h1 = mfma4(wl[6 + t], e, h1);
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -210,7 +285,8 @@ __device__ __forceinline__ float stage32(const float (&x)[10], const f32x4 (&u)[
     transpose4(h1);
     f32x4 c = W.b2;
 #pragma unroll
-    for (int t = 0; t < 8; ++t) c = mfma4(W.w2[t], t < 4 ? h0[t] : h1[t - 4], c);
+    for (int t = 0; t < 8; ++t) c = mfma4(wl[12 + t], t < 4 ? h0[t] : h1[t - 4], c);
+    __builtin_amdgcn_s_setprio(0);
     // coefficients 0..3 of the chain in lane group 0, then 4..7 in group 1
     float v = 0.f;
 #pragma unroll
@@ -230,6 +306,9 @@ struct Fp32Shared {
     uint4 xs[F32_WAVES][FP32_TILE * F32_ROW / 16];  // one stage's feature rows of each wave
     float v[2][F32_CHUNK][FP32_TILE];               // stage costs of two chunks
     float2 carry[FP32_TILE];                        // (sum, compensation) between chunks
+    LogEntry log[LOG32_N];
+    float4 w[5][64];                      // operands of the second and third layer
+    float list[F32_WAVES][LIST32 + 64];  // values whose logarithm log1pf takes
 };
 
 // Loads of one wave's stage, issued one stage ahead of its arithmetic: the
@@ -262,11 +341,13 @@ static_assert(FP32_TILE * F32_ROW == 2560, "three copies of 1,024 + 1,024 + 512 
 // (wave w: w, w + 8, ...), write the stage costs to LDS, and one wave, a
 // different one for each chunk of stages, adds them in ascending order with
 // compensation while the others go on.
-// Bound by the vector ALU: log1pf is about 75 instructions a value (300 cycles
-// a wave and SIMD), 10 values a lane and stage, against 40 matrix
-// instructions of 32 cycles.  One query of 30 x 6,400: 515 us with one thread
-// per candidate (100 waves, each a serial walk over the stages), 38 us so;
-// 4 x 64: 80 us and 11 us.
+// Bound by the vector ALU and the matrix cores, which overlap little: about 400
+// vector instructions a wave and stage, 270 of them for the logarithms of its
+// 10 values a lane (log1pf itself is 75 a value), and 40 matrix instructions of
+// 32 cycles.  One query of 30 x 6,400: 515 us with one thread per candidate
+// (100 waves, each a serial walk over the stages), 42 us in tiles with log1pf
+// for every value, 31 us so; 4 x 64: 80, 6.5 and 6.0 us; 64 x 32,768 with its
+// selection: 304 us with log1pf, 201 us so.
 __global__ __launch_bounds__(F32_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 k_eval_fp32(EvalLaunch L, const Fp32Pack *__restrict__ pk, const float *sched, const float *terms,
             const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage)
@@ -278,6 +359,9 @@ k_eval_fp32(EvalLaunch L, const Fp32Pack *__restrict__ pk, const float *sched, c
     const Fp32Weights W = load_fp32(pk, lane);
     uint4 *xsw = sh.xs[wave];
     const float *xw = reinterpret_cast<const float *>(xsw);
+    for (int i = threadIdx.x; i < LOG32_N; i += F32_WAVES * 64) sh.log[i] = pk->log[i];
+    if (threadIdx.x < 5 * 64) sh.w[0][threadIdx.x] = pk->w[5][threadIdx.x];
+    __syncthreads();
     int round = 0;
     for (int task = blockIdx.x; task < L.ntasks; task += gridDim.x) {
         const int q = query_at(L.nq, task, [&](int j) { return L.q[j].task0; });
@@ -304,7 +388,8 @@ k_eval_fp32(EvalLaunch L, const Fp32Pack *__restrict__ pk, const float *sched, c
                 if (s + F32_WAVES < c1)
                     issue32(Q, sched, terms, U, s + F32_WAVES, i0, rows, lane, xsw, u, tr);
                 asm volatile("" ::: "memory");
-                const float v = stage32(x, u0, t0, W);
+                log1p_wave(x, sh.log, sh.list[wave]);
+                const float v = stage32(x, u0, t0, W, sh.w);
                 if (g == 1) {
                     vb[s - c0][n] = v;
                     if (stage && n < rows) stage[Q.stage_off + (int64_t)s * Q.N + i0 + n] = v;

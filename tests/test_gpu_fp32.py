@@ -57,3 +57,57 @@ def test_fp32_split_edges(oracle_mod, shapes):
         assert np.all(np.abs(mine - ref) <= COEF_TOL * tsum.sum(axis=0)), (S, N)
         assert np.median(gc.rel_err(mine, ref)) <= MEDIAN_TOL, (S, N)
     ws.close()
+
+
+def _log_values():
+    """Values of every exponent, ends and special values of float32, and runs of
+    neighbours (among which are the roundings nearest to a tie)."""
+    rng = np.random.default_rng(14)
+    bits = [rng.integers(e << 23, (e + 1) << 23, 400) for e in range(1, 255)]
+    for x in (2.0 ** -28, 2.0 ** -6, 0.5, 1.0, 3.0, 7.0, 15.0, 55.0, 63.0, 1e4, 65535.0, 2.0 ** 64):
+        at = int(np.float32(x).view(np.uint32))
+        bits.append(np.arange(at - 4000, at + 4000))
+    bits.append([0, 0x80000000, 1, 0x007fffff, 0x7f7fffff, 0xbf000000, 0xbe000001, 0xbf7fffff,
+                 0xbf800000, 0xc0000000, 0x7fc00000, 0xb8000000])
+    v = np.concatenate([np.asarray(b, np.int64) for b in bits]).astype(np.uint32)
+    return v.view(np.float32)
+
+
+@pytest.mark.parametrize("mix", ["alone", "beside_plain", "beside_zero"])
+def test_fp32_log_has_the_bits_of_log1pf(mix):
+    """The logarithm of a schedule feature (short form and gathered log1pf)
+    against that of an algorithm feature (log1pf), each routed to the stage's
+    cost with unit weights: one value per stage, the same bits, whatever values
+    are beside it in its wave."""
+    import torch
+    import paper_2012_07145_amd as cm
+    from synth import Query
+    from tests import cmcases as cc
+    x = _log_values()
+    S, N = x.size, 3
+    sched = np.zeros((S, N, 40), np.float32)
+    if mix == "beside_plain":
+        sched[:] = np.exp(np.random.default_rng(3).normal(4.0, 2.0, (S, N, 40)))
+    sched[:, 1, 0] = x
+    terms = np.zeros((S, N, 8), np.float32)
+    terms[:, :, 0] = 1.0
+    got = {}
+    for route in ("sched", "pipe"):
+        pipe = np.zeros((S, 56), np.float32)
+        if route == "pipe":
+            pipe[:, 0] = x
+        q = Query(pipe, sched if route == "sched" else np.zeros_like(sched), terms)
+        if mix == "alone" and route == "sched":
+            q.sched[:, 0], q.sched[:, 2] = -0.25, 1e6  # neighbours that log1pf takes
+        m = cm.cm_model_create(cc.log_params(route))
+        ws = gc.workspace_for(cm, [q])
+        batch, cost = cm.pack_queries([q], "fp32")
+        stage = torch.empty(S * N, device="cuda")
+        cm.cm_eval_stages(m, "fp32", batch, ws, cost, stage)
+        torch.cuda.synchronize()
+        got[route] = stage.view(S, N)[:, 1].cpu().numpy()
+        ws.close()
+        m.close()
+    same = got["sched"].view(np.uint32) == got["pipe"].view(np.uint32)
+    same |= np.isnan(got["sched"]) & np.isnan(got["pipe"])
+    assert np.all(same), (x[~same][:5], got["sched"][~same][:5], got["pipe"][~same][:5])
