@@ -400,18 +400,19 @@ cm_status cm_fp8_encode(const float *x, int64_t n, float in_scale, uint8_t *code
 
 /* ------------------------------------------------------------------------
  * Persistent beam step: hoist + evaluate + select for a ragged batch in one
- * persistent launch that is replayed as a HIP graph.
+ * persistent launch.
  *
  * A step object owns device descriptors, control words and selection lists
- * for `slots` steps that may be in flight at once.  cm_step_run writes the
- * batch's descriptors into pinned host memory; the step then runs as
- *   copy of the descriptors to the device -> hoist (only when U is NULL) ->
+ * for `slots` steps that may be in flight at once.  The step runs as
+ *   hoist (only when U is NULL) ->
  *   one persistent CM_BF16 or CM_FP8 evaluation kernel whose workgroups take tasks
  *   from a device-wide queue, with each query's top-k selection run by the
- *   workgroup that finishes the query's last task,
- * either as one graph launch (captured once per slot and configuration) or
- * as plain launches.  The launch shape depends only on the configuration,
- * never on the batch.  Results are bit-identical to cm_eval_batch /
+ *   workgroup that finishes the query's last task.
+ * A batch of up to 32 queries passes its descriptors in the kernels' arguments,
+ * as plain launches.  A larger batch's descriptors are written into pinned
+ * host memory and copied to the device first, either all as one graph launch
+ * (captured once per slot and configuration, its shape never depending on the
+ * batch) or as plain launches.  Results are bit-identical to cm_eval_batch /
  * cm_eval_hoisted (same precision) followed by cm_topk_per_query, for every
  * configuration.
  * ------------------------------------------------------------------------ */
@@ -431,7 +432,8 @@ typedef struct {
                              compute unit */
     int32_t group_tiles;  /* row-tile groups per task: 1, 2, 4 or 8 (a group is
                              8 / P tiles of 32 candidates) */
-    int32_t use_graph;    /* 1: replay a captured graph; 0: plain launches */
+    int32_t use_graph;    /* of more than 32 queries, 1: replay a captured graph;
+                             0: plain launches */
 } cm_step_config;
 
 /* Create a step on the current device for `model`, which must outlive it.
@@ -651,9 +653,8 @@ cm_status cm_server_fail_next_launch(cm_server *server);
  * cm_step_config), for example the one cm_step_autotune or a short trial
  * of the caller picks for its traffic.  The default is the tuning cache's
  * entry for the server's max_batch_queries (cm_step_tuned_config), else
- * {grid 0 (two workgroups per compute unit), group_tiles 1, use_graph 1}; plain launches
- * (use_graph 0) cost a lone request less time per micro-batch.  Takes effect
- * for micro-batches launched afterwards; results never depend on it.
+ * {grid 0 (two workgroups per compute unit), group_tiles 1, use_graph 1}.
+ * Takes effect for micro-batches launched afterwards; results never depend on it.
  * Errors: CM_EINVAL. */
 cm_status cm_server_set_step_config(cm_server *server, const cm_step_config *cfg);
 cm_status cm_server_get_step_config(const cm_server *server, cm_step_config *cfg);

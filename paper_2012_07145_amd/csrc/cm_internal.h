@@ -233,6 +233,15 @@ struct StepHead {
 };
 static_assert(sizeof(StepHead) == 32, "step head layout");
 
+// Descriptors of a step that go to its kernels by value: as many as a kernel's
+// arguments (4 KB) hold.
+constexpr int STEP_VALUE_QUERIES = 32;
+struct StepArgs {
+    StepHead h;
+    StepQ q[STEP_VALUE_QUERIES];
+};
+static_assert(sizeof(StepArgs) <= 4096 - 64, "kernel arguments");
+
 // Control words of a step, zero between steps (the step kernel leaves them
 // zero when it ends): task queue head, exit count, per-query and per-tile
 // arrival counts.
@@ -306,6 +315,11 @@ hipError_t launch_step_hoist(const StepHead *h, const StepQ *qs, const Model &m,
                              cm_precision prec, int grid, hipStream_t st);
 hipError_t launch_step(const StepHead *h, const StepQ *qs, uint32_t *ctl, uint64_t *tpart,
                        const Model &m, cm_precision prec, int grid, hipStream_t st);
+// The same by value (a.h.nq <= STEP_VALUE_QUERIES).
+hipError_t launch_step_hoist(const StepArgs &a, const Model &m, cm_precision prec,
+                             hipStream_t st);
+hipError_t launch_step(const StepArgs &a, uint32_t *ctl, uint64_t *tpart, const Model &m,
+                       cm_precision prec, int grid, hipStream_t st);
 
 // Device side: data one workgroup hands to another inside a launch (costs
 // read by the selecting workgroup, per-tile beam lists) is stored and loaded

@@ -142,11 +142,11 @@ cm_status check_step_batch(const cm_step &S, const cm_batch *b, const float *U, 
     return CM_OK;
 }
 
-// Descriptors of the queries into the slot's pinned block.  Tasks are issued
+// Descriptors of the queries into *h and qs.  Tasks are issued
 // longest stage part first; each query's outputs stay where its request
 // points.
-void fill_descriptors(const cm_step &S, Slot &sl, const cm::StepReq *r, int nq, int32_t k,
-                      bool hoist, uint64_t *clk_out)
+void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm::StepReq *r,
+                      int nq, int32_t k, bool hoist, uint64_t *clk_out)
 {
     using namespace cm;
     std::vector<int32_t> order(nq);
@@ -159,8 +159,6 @@ void fill_descriptors(const cm_step &S, Slot &sl, const cm::StepReq *r, int nq, 
                      [&](int32_t x, int32_t y) { return per_wave(x) > per_wave(y); });
 
     const int gpt = S.cfg.group_tiles;
-    StepHead *h = head_of(sl.h_block);
-    StepQ *qs = queries_of(sl.h_block);
     std::memset(h, 0, sizeof *h);
     int64_t task = 0, row = 0, tile = 0;
     for (int j = 0; j < nq; ++j) {
@@ -243,6 +241,23 @@ cm_status get_exec(cm_step &S, Slot &sl, bool hoist, hipGraphExec_t *out)
     return CM_OK;
 }
 
+// Whether a step of n queries goes straight to its kernels: descriptors in
+// their arguments, without the slot's block, its copy and the graph.  The copy
+// took 5 us and every edge of the graph 4 us, more than many a batch's
+// arithmetic: one query of 20 x 200 took 35.3 us through the block and takes
+// 26.3 us so, 17 ragged queries 54.2 and 43.5, 32 of them 79 and 66.  As many
+// queries go this way as the arguments hold.  A replay in a stream under
+// capture is left to the graph launch, which refuses it.
+bool by_value(const cm_step &S, int n, hipStream_t st)
+{
+    if (n > cm::STEP_VALUE_QUERIES) return false;
+    if (!S.cfg.use_graph) return true;
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &c) == hipSuccess) return c == hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return false;
+}
+
 cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool hoist,
                         hipStream_t st, uint64_t *clk_out = nullptr)
 {
@@ -250,15 +265,23 @@ cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool
     Slot &sl = S.slot[S.next];
     if (sl.pending) CM_HIP(hipEventSynchronize(sl.done));  // its descriptors are still read
     sl.pending = false;
-    fill_descriptors(S, sl, r, n, k, hoist, clk_out);
-    if (S.cfg.use_graph) {
-        hipGraphExec_t ex = nullptr;
-        cm_status rc = get_exec(S, sl, hoist, &ex);
-        if (rc != CM_OK) return rc;
-        CM_HIP(hipGraphLaunch(ex, st));
+    if (by_value(S, n, st)) {
+        cm::StepArgs a;
+        fill_descriptors(S, &a.h, a.q, r, n, k, hoist, clk_out);
+        std::memset(a.q + n, 0, (cm::STEP_VALUE_QUERIES - n) * sizeof(cm::StepQ));
+        CM_HIP(cm::launch_step_hoist(a, S.model->m, S.prec, st));
+        CM_HIP(cm::launch_step(a, sl.d_ctl, sl.d_tpart, S.model->m, S.prec, grid_of(S), st));
     } else {
-        const size_t bytes = sizeof(cm::StepHead) + (size_t)n * sizeof(cm::StepQ);
-        CM_HIP(issue(S, sl, hoist, bytes, st));
+        fill_descriptors(S, head_of(sl.h_block), queries_of(sl.h_block), r, n, k, hoist, clk_out);
+        if (S.cfg.use_graph) {
+            hipGraphExec_t ex = nullptr;
+            cm_status rc = get_exec(S, sl, hoist, &ex);
+            if (rc != CM_OK) return rc;
+            CM_HIP(hipGraphLaunch(ex, st));
+        } else {
+            const size_t bytes = sizeof(cm::StepHead) + (size_t)n * sizeof(cm::StepQ);
+            CM_HIP(issue(S, sl, hoist, bytes, st));
+        }
     }
     CM_HIP(hipEventRecord(sl.done, st));
     sl.pending = true;

@@ -89,6 +89,21 @@ __global__ __launch_bounds__(64) void k_hoist_step(const StepHead *__restrict__ 
     }
 }
 
+// The same for descriptors in the kernel's arguments, one row per workgroup.
+__global__ __launch_bounds__(64) void k_hoist_step_value(StepArgs a,
+                                                         const float *__restrict__ params,
+                                                         const float *__restrict__ beta,
+                                                         const float *__restrict__ scale)
+{
+    static_assert(STEP_VALUE_QUERIES <= 64, "one lane per query");
+    __shared__ float lp[FP];
+    __shared__ float ep[E];
+    const int q = query_at(a.h.nq, blockIdx.x, [&](int j) { return a.q[j].row0; });
+    const int s = blockIdx.x - a.q[q].row0;
+    hoist_row(params, beta, 1, scale ? *scale : 1.f, a.q[q].pipe + (int64_t)s * FP,
+              a.q[q].u + (int64_t)s * H, lp, ep);
+}
+
 // ---- float32 evaluator ----
 // Every sum is the same chain of fused multiply-adds, in the same order, that
 // a scalar walk over features, embedding and hidden units gives: one
@@ -436,6 +451,15 @@ hipError_t launch_step_hoist(const StepHead *h, const StepQ *qs, const Model &m,
     const float *scale = prec == CM_FP8 ? &m.d_fp8->uh : nullptr;
     hipLaunchKernelGGL(k_hoist_step, dim3(grid), dim3(64), 0, st, h, qs, m.d->params, m.d->beta,
                        scale);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_hoist(const StepArgs &a, const Model &m, cm_precision prec, hipStream_t st)
+{
+    if (a.h.nrows == 0) return hipSuccess;
+    const float *scale = prec == CM_FP8 ? &m.d_fp8->uh : nullptr;
+    hipLaunchKernelGGL(k_hoist_step_value, dim3(a.h.nrows), dim3(64), 0, st, a, m.d->params,
+                       m.d->beta, scale);
     return hipGetLastError();
 }
 

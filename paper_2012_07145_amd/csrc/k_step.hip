@@ -1,8 +1,9 @@
 // k_step.hip -- the persistent step kernel: bf16 or FP8 evaluation of many
 // ragged queries (Sec. 5.2) and each query's beam selection (Sec. 4, Sec. 4.4)
-// in one launch whose shape never depends on the batch.
+// in one launch.
 //
-// A fixed grid of workgroups (8 waves each) takes tasks from a device-wide
+// A grid of workgroups (8 waves each) whose size the batch may only reduce
+// takes tasks from a device-wide
 // queue (one atomic add per task, taken when the previous task ends).  A task is `gpt`
 // consecutive row-tile groups of one query, evaluated exactly as the
 // per-call kernels do (eval_bf16.h, eval_fp8.h), so the costs are
@@ -13,6 +14,8 @@
 // finish merges their lists.  A query's selection therefore runs while other queries are
 // still being evaluated.  All control words are left at zero when the
 // kernel ends, so the next launch needs no clearing.
+#include <algorithm>
+
 #include "eval_bf16.h"
 #include "eval_fp8.h"
 #include "topk_dev.h"
@@ -218,6 +221,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     step_body(h, qs, ctl, tpart, pk);
 }
 
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+k_step_bf16_value(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Bf16Pack *__restrict__ pk)
+{
+    step_body(&a.h, a.q, ctl, tpart, pk);
+}
+
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+k_step_fp8_value(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Fp8Pack *__restrict__ pk)
+{
+    step_body(&a.h, a.q, ctl, tpart, pk);
+}
+
 }  // namespace
 
 hipError_t launch_step(const StepHead *h, const StepQ *qs, uint32_t *ctl, uint64_t *tpart,
@@ -227,6 +242,18 @@ hipError_t launch_step(const StepHead *h, const StepQ *qs, uint32_t *ctl, uint64
         hipLaunchKernelGGL(k_step_fp8, dim3(grid), dim3(NT), 0, st, h, qs, ctl, tpart, m.d_fp8);
     else
         hipLaunchKernelGGL(k_step_bf16, dim3(grid), dim3(NT), 0, st, h, qs, ctl, tpart,
+                           &m.d->bf16);
+    return hipGetLastError();
+}
+
+hipError_t launch_step(const StepArgs &a, uint32_t *ctl, uint64_t *tpart, const Model &m,
+                       cm_precision prec, int grid, hipStream_t st)
+{
+    grid = std::min(grid, a.h.ntasks);  // a workgroup without a task would only leave
+    if (prec == CM_FP8)
+        hipLaunchKernelGGL(k_step_fp8_value, dim3(grid), dim3(NT), 0, st, a, ctl, tpart, m.d_fp8);
+    else
+        hipLaunchKernelGGL(k_step_bf16_value, dim3(grid), dim3(NT), 0, st, a, ctl, tpart,
                            &m.d->bf16);
     return hipGetLastError();
 }
