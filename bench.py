@@ -95,8 +95,8 @@ def parse():
                     help="skip the same serving workload in the FP8 form")
     ap.add_argument("--slots", type=int, default=3, help="serving micro-batches in flight")
     ap.add_argument("--serve-graph", type=int, choices=(0, 1), default=None,
-                    help="server steps as a replayed HIP graph (1) or plain launches (0); "
-                         "default: the library's")
+                    help="use_graph of the server's step configuration, which the library "
+                         "keeps and reports; its steps are plain launches either way")
     ap.add_argument("--max-batch-queries", type=int, default=128)
     ap.add_argument("--copy-calibration", action="store_true",
                     help="only run a 1 GiB device copy (HBM counter calibration)")

@@ -408,11 +408,9 @@ cm_status cm_fp8_encode(const float *x, int64_t n, float in_scale, uint8_t *code
  *   one persistent CM_BF16 or CM_FP8 evaluation kernel whose workgroups take tasks
  *   from a device-wide queue, with each query's top-k selection run by the
  *   workgroup that finishes the query's last task.
- * A batch of up to 32 queries passes its descriptors in the kernels' arguments,
- * as plain launches.  A larger batch's descriptors are written into pinned
- * host memory and copied to the device first, either all as one graph launch
- * (captured once per slot and configuration, its shape never depending on the
- * batch) or as plain launches.  Results are bit-identical to cm_eval_batch /
+ * A batch of up to 32 queries passes its descriptors in the kernels' arguments;
+ * a larger batch's are written into pinned host memory and copied to the device
+ * first.  Results are bit-identical to cm_eval_batch /
  * cm_eval_hoisted (same precision) followed by cm_topk_per_query, for every
  * configuration.
  * ------------------------------------------------------------------------ */
@@ -432,8 +430,9 @@ typedef struct {
                              compute unit */
     int32_t group_tiles;  /* row-tile groups per task: 1, 2, 4 or 8 (a group is
                              8 / P tiles of 32 candidates) */
-    int32_t use_graph;    /* of more than 32 queries, 1: replay a captured graph;
-                             0: plain launches */
+    int32_t use_graph;    /* 0 or 1; kept and reported, of no effect: a step is
+                             plain launches, which cost less than a graph of
+                             the same work for every batch */
 } cm_step_config;
 
 /* Create a step on the current device for `model`, which must outlive it.
@@ -469,7 +468,7 @@ cm_status cm_step_get_config(const cm_step *step, cm_step_config *cfg);
 
 /* Autotuner: times every configuration of a built-in candidate set on this
  * batch (grid 1, 2 and 4 workgroups per compute unit x group_tiles 1, 2, 4,
- * 8 x graph replay or plain launches; `reps` timed runs each after one
+ * 8; `reps` timed runs each after one
  * untimed run, median of HIP event times on `stream`), keeps the fastest as
  * the step's configuration and returns it in *best (and its median time in
  * microseconds in *best_us, if not NULL).  The pick is also stored in the

@@ -288,7 +288,7 @@ def cm_topk_per_query(cost, batch: Batch, k: int, ws: Workspace, idx_out, val_ou
 
 
 class Step:
-    """Handle of a cm_step (persistent, graph-replayed beam step)."""
+    """Handle of a cm_step (persistent beam step)."""
 
     def __init__(self, handle, model):
         self.handle = handle
@@ -322,7 +322,7 @@ def cm_step_destroy(step: Step):
 
 def cm_step_run(step: Step, batch: Batch, U, k: int, cost_out, idx_out, val_out, stream=None):
     """Hoist (when U is None) + evaluate + select for every query of the
-    batch, as one persistent launch (replayed as a graph by default)."""
+    batch, as one persistent launch."""
     check(lib().cm_step_run(step.handle, ctypes.byref(batch.c), _ptr(U), int(k), _ptr(cost_out),
                             _ptr(idx_out), _ptr(val_out), _stream_handle(stream)))
 

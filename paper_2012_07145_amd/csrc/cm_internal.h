@@ -194,10 +194,10 @@ struct TopkLaunch {
 };
 
 // ------------------------------------------------------------------ step
-// Device-resident descriptors of one persistent step (hoist + evaluate +
-// select).  The host writes them into pinned memory and one copy moves them
-// to the device ahead of the kernels, so the launch configuration never
-// depends on the batch and the whole step can be replayed as a graph.
+// Descriptors of one persistent step (hoist + evaluate + select), in the
+// kernels' arguments or, for more queries than they hold, in device memory:
+// the host writes them into pinned memory and one copy moves them ahead of the
+// kernels.
 constexpr int STEP_MAX_QUERIES = CM_STEP_MAX_QUERIES;
 
 struct StepQ {

@@ -110,7 +110,7 @@ public:
         return true;
     }
 
-    // the slot streams and graphs belong to the server's device: a thread
+    // the slot streams belong to the server's device: a thread
     // whose current device is another one leaves the launch to the worker
     bool launch_here() override
     {

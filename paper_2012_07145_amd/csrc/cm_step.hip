@@ -1,5 +1,5 @@
 // cm_step.hip -- host side of the persistent beam step (include/cm.h):
-// descriptor slots in pinned memory, graph capture and replay, autotuner.
+// descriptors by value or in slots, launches, autotuner.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -24,8 +24,6 @@ struct Slot {
     uint32_t *d_ctl = nullptr;         // control words (zero between steps)
     uint64_t *d_tpart = nullptr;       // per-tile beam lists
     float *d_U = nullptr;              // hoisted rows when the caller gives none
-    hipGraphExec_t exec[2] = {nullptr, nullptr};  // [with hoist]
-    int exec_grid[2] = {0, 0};
     hipEvent_t done = nullptr;         // recorded after the slot's last step
     bool pending = false;
 };
@@ -46,7 +44,6 @@ struct cm_step {
     char arch[64] = {0};  // the device's gcnArchName (key of the tuning cache)
     int64_t max_tiles = 0;
     size_t block_bytes = 0;
-    hipStream_t cs = nullptr;  // capture stream
     Slot slot[MAX_SLOTS];
     int next = 0;
     int last = -1;  // slot of the most recent step
@@ -59,8 +56,6 @@ size_t ctl_words(const cm_step &S) { return (size_t)cm::CTL_TCNT + (size_t)S.max
 
 int grid_of(const cm_step &S) { return S.cfg.grid > 0 ? S.cfg.grid : 2 * S.cus; }
 
-int hoist_grid(const cm_step &S) { return (int)std::min<int64_t>(S.cap.max_stages, 4 * S.cus); }
-
 cm::StepHead *head_of(unsigned char *block) { return reinterpret_cast<cm::StepHead *>(block); }
 cm::StepQ *queries_of(unsigned char *block)
 {
@@ -69,8 +64,6 @@ cm::StepQ *queries_of(unsigned char *block)
 
 void free_slot(Slot &s)
 {
-    for (auto &e : s.exec)
-        if (e) (void)hipGraphExecDestroy(e);
     if (s.done) (void)hipEventDestroy(s.done);
     if (s.h_block) (void)hipHostFree(s.h_block);
     if (s.d_block) (void)hipFree(s.d_block);
@@ -83,7 +76,6 @@ void free_slot(Slot &s)
 void free_step(cm_step *S)
 {
     for (auto &s : S->slot) free_slot(s);
-    if (S->cs) (void)hipStreamDestroy(S->cs);
     delete S;
 }
 
@@ -195,67 +187,23 @@ void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm
     h->clk_out = clk_out;
 }
 
-// The device work of one step on `st`: descriptor copy, hoist, step kernel.
-hipError_t issue(const cm_step &S, Slot &sl, bool hoist, size_t bytes, hipStream_t st)
+// The device work of one step whose descriptors are in the slot's block: their
+// copy, hoist, step kernel.
+hipError_t issue(const cm_step &S, Slot &sl, int n, hipStream_t st)
 {
     using namespace cm;
     const StepHead *h = reinterpret_cast<const StepHead *>(sl.d_block);
     const StepQ *qs = reinterpret_cast<const StepQ *>(sl.d_block + sizeof(StepHead));
+    const size_t bytes = sizeof(StepHead) + (size_t)n * sizeof(StepQ);
+    const StepHead &head = *head_of(sl.h_block);
     hipError_t e = hipMemcpyAsync(sl.d_block, sl.h_block, bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return e;
-    if (hoist &&
-        (e = launch_step_hoist(h, qs, S.model->m, S.prec, hoist_grid(S), st)) != hipSuccess)
+    if (head.nrows > 0 &&
+        (e = launch_step_hoist(h, qs, S.model->m, S.prec, std::min(head.nrows, 4 * S.cus), st)) !=
+            hipSuccess)
         return e;
-    return launch_step(h, qs, sl.d_ctl, sl.d_tpart, S.model->m, S.prec, grid_of(S), st);
-}
-
-cm_status get_exec(cm_step &S, Slot &sl, bool hoist, hipGraphExec_t *out)
-{
-    const int g = grid_of(S);
-    hipGraphExec_t &ex = sl.exec[hoist ? 1 : 0];
-    if (ex && sl.exec_grid[hoist ? 1 : 0] == g) {
-        *out = ex;
-        return CM_OK;
-    }
-    if (ex) {
-        (void)hipGraphExecDestroy(ex);
-        ex = nullptr;
-    }
-    CM_HIP(hipStreamBeginCapture(S.cs, hipStreamCaptureModeThreadLocal));
-    const hipError_t e = issue(S, sl, hoist, S.block_bytes, S.cs);
-    hipGraph_t graph = nullptr;
-    const hipError_t e2 = hipStreamEndCapture(S.cs, &graph);
-    if (e != hipSuccess || e2 != hipSuccess) {
-        if (graph) (void)hipGraphDestroy(graph);
-        return fail(CM_EDEVICE, "step capture failed: %s",
-                    hipGetErrorString(e != hipSuccess ? e : e2));
-    }
-    const hipError_t e3 = hipGraphInstantiate(&ex, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
-    if (e3 != hipSuccess) {
-        ex = nullptr;
-        return fail(CM_EDEVICE, "graph instantiation failed: %s", hipGetErrorString(e3));
-    }
-    sl.exec_grid[hoist ? 1 : 0] = g;
-    *out = ex;
-    return CM_OK;
-}
-
-// Whether a step of n queries goes straight to its kernels: descriptors in
-// their arguments, without the slot's block, its copy and the graph.  The copy
-// took 5 us and every edge of the graph 4 us, more than many a batch's
-// arithmetic: one query of 20 x 200 took 35.3 us through the block and takes
-// 26.3 us so, 17 ragged queries 54.2 and 43.5, 32 of them 79 and 66.  As many
-// queries go this way as the arguments hold.  A replay in a stream under
-// capture is left to the graph launch, which refuses it.
-bool by_value(const cm_step &S, int n, hipStream_t st)
-{
-    if (n > cm::STEP_VALUE_QUERIES) return false;
-    if (!S.cfg.use_graph) return true;
-    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &c) == hipSuccess) return c == hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return false;
+    return launch_step(h, qs, sl.d_ctl, sl.d_tpart, S.model->m, S.prec,
+                       std::min(grid_of(S), head.ntasks), st);
 }
 
 cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool hoist,
@@ -265,7 +213,13 @@ cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool
     Slot &sl = S.slot[S.next];
     if (sl.pending) CM_HIP(hipEventSynchronize(sl.done));  // its descriptors are still read
     sl.pending = false;
-    if (by_value(S, n, st)) {
+    // Up to as many descriptors as a kernel's arguments hold go to the kernels
+    // by value: their copy and the kernel boundary after it take 8 to 9 us, 32
+    // queries 66 us so and 70 us through the slot's block.  Both ways are plain
+    // launches: a graph of the same work took 7 us more for every batch, with 4
+    // us at each of its edges (33 queries 77.5 us and 70.5, 128 hoisted ones 199
+    // and 192, in FP8 136 and 128).
+    if (n <= cm::STEP_VALUE_QUERIES) {
         cm::StepArgs a;
         fill_descriptors(S, &a.h, a.q, r, n, k, hoist, clk_out);
         std::memset(a.q + n, 0, (cm::STEP_VALUE_QUERIES - n) * sizeof(cm::StepQ));
@@ -273,15 +227,7 @@ cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool
         CM_HIP(cm::launch_step(a, sl.d_ctl, sl.d_tpart, S.model->m, S.prec, grid_of(S), st));
     } else {
         fill_descriptors(S, head_of(sl.h_block), queries_of(sl.h_block), r, n, k, hoist, clk_out);
-        if (S.cfg.use_graph) {
-            hipGraphExec_t ex = nullptr;
-            cm_status rc = get_exec(S, sl, hoist, &ex);
-            if (rc != CM_OK) return rc;
-            CM_HIP(hipGraphLaunch(ex, st));
-        } else {
-            const size_t bytes = sizeof(cm::StepHead) + (size_t)n * sizeof(cm::StepQ);
-            CM_HIP(issue(S, sl, hoist, bytes, st));
-        }
+        CM_HIP(issue(S, sl, n, st));
     }
     CM_HIP(hipEventRecord(sl.done, st));
     sl.pending = true;
@@ -487,11 +433,6 @@ cm_status cm_step_create(const cm_model *model, cm_precision prec, const cm_step
     }
     S->cus = prop.multiProcessorCount;
     std::snprintf(S->arch, sizeof S->arch, "%s", prop.gcnArchName);
-    if (hipStreamCreateWithFlags(&S->cs, hipStreamNonBlocking) != hipSuccess) {
-        S->cs = nullptr;
-        free_step(S);
-        return fail(CM_EDEVICE, "stream creation failed");
-    }
     for (int i = 0; i < d->slots; ++i) {
         Slot &sl = S->slot[i];
         bool ok = hipHostMalloc((void **)&sl.h_block, S->block_bytes, hipHostMallocDefault) ==
@@ -577,9 +518,9 @@ cm_status cm_step_autotune(cm_step *S, const cm_batch *b, const float *U, int32_
     if (rc != CM_OK) return rc;
     const cm_step_config saved = S->cfg;
     std::vector<cm_step_config> cands;
-    for (int graph : {1, 0})
-        for (int gm : {1, 2, 4})
-            for (int gt : {1, 2, 4, 8}) cands.push_back(cm_step_config{gm * S->cus, gt, graph});
+    for (int gm : {1, 2, 4})
+        for (int gt : {1, 2, 4, 8})
+            cands.push_back(cm_step_config{gm * S->cus, gt, saved.use_graph});
     std::vector<hipEvent_t> ev(2 * (size_t)reps, nullptr);
     for (auto &e : ev)
         if (hipEventCreate(&e) != hipSuccess) {

@@ -61,7 +61,7 @@ __global__ __launch_bounds__(64) void k_hoist(EvalLaunch L, const float *__restr
 // Hoist of a step: the rows of every query, grid-stride, from the device
 // descriptors (the folded form of the bf16 and FP8 evaluators, with
 // W_1[:, 24:] b_s folded in), times *scale when given (the FP8 form's s_h,
-// read at run time so that a replayed graph follows the model's form).
+// read at run time so that a recorded launch follows the model's form).
 __global__ __launch_bounds__(64) void k_hoist_step(const StepHead *__restrict__ h,
                                                    const StepQ *__restrict__ qs,
                                                    const float *__restrict__ params,

@@ -1,8 +1,8 @@
 """Steps of up to 32 queries, whose descriptors go to the kernels by value,
 and of more, which go through the slot's block: both equal the per-call path
 bit for bit, at the edge between the two, in both precisions, with the step's
-own hoist and with given rows, as graph replays and as plain launches, and with
-slots reused between batches of either kind."""
+own hoist and with given rows, under either value of use_graph, and with slots
+reused between batches of either kind."""
 import numpy as np
 import pytest
 
