@@ -213,7 +213,7 @@ struct StepQ {
     int32_t S, N;
     int32_t task0;      // first task of this query
     int32_t ntasks;     // >= 1 (a query with no candidates still writes its padding)
-    int32_t parts;      // stage parts P
+    int32_t parts;      // waves that share a row tile: stage_parts(S), or all 8
     int32_t row0;       // first hoist row of this query
     int32_t tile0;      // first selection tile (global numbering)
     int32_t ntiles;     // selection tiles of TOPK_TILE candidates, >= 1
@@ -225,7 +225,7 @@ struct StepHead {
     int32_t nrows;     // hoist rows over all queries
     int32_t k;         // beam width
     int32_t gpt;       // row-tile groups per task (1, 2 or 4)
-    int32_t pad;
+    int32_t spread;    // tiles of queries of up to SPREAD_STAGES stages take all waves
     // where the launch's (first start, last end) clock pair also goes, or
     // null: host memory mapped for the device, so a server learns it without
     // a copy

@@ -134,6 +134,30 @@ cm_status check_step_batch(const cm_step &S, const cm_batch *b, const float *U, 
     return CM_OK;
 }
 
+// Whether every row tile of a batch should have all waves of a workgroup,
+// which share its stages.  Where the tiles are fewer than the compute units,
+// a wave's stages one after the other (1.0 us each in bf16) are the step: one
+// query of 20 x 200 takes 26.1 us with 10 stages a wave and 20.1 us with 3, 30
+// x 8,000 (250 tiles) 35.4 and 28.9, in FP8 20 x 200 21.0 and 16.8.  Beyond one
+// tile per compute unit the chip is filled either way and the waves that share
+// tiles only add workgroups: 33 x 12,000 (375 tiles) took 31.6 and 34.5 us.
+// Fewer than 4 stages saved do not pay the sums' second walk (3 x 200: 18.6 and
+// 20.4 us; 5 x 200, 4 saved: 19.6 and 17.8).
+bool spread_pays(const cm::StepReq *r, int nq, int max_tiles)
+{
+    using namespace cm;
+    if (nq > STEP_VALUE_QUERIES) return false;
+    int64_t tiles = 0;
+    int chain = 0, shared = 0;  // most stages of a wave either way
+    for (int q = 0; q < nq; ++q) {
+        tiles += cdiv(r[q].N, TILE_ROWS);
+        if (r[q].N == 0) continue;
+        chain = std::max<int>(chain, (int)cdiv(r[q].S, stage_parts(r[q].S)));
+        shared = std::max<int>(shared, (int)cdiv(r[q].S, EVAL_WAVES));
+    }
+    return tiles <= max_tiles && chain - shared >= 4;
+}
+
 // Descriptors of the queries into *h and qs.  Tasks are issued
 // longest stage part first; each query's outputs stay where its request
 // points.
@@ -151,6 +175,7 @@ void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm
                      [&](int32_t x, int32_t y) { return per_wave(x) > per_wave(y); });
 
     const int gpt = S.cfg.group_tiles;
+    const bool spread = spread_pays(r, nq, S.cus);
     std::memset(h, 0, sizeof *h);
     int64_t task = 0, row = 0, tile = 0;
     for (int j = 0; j < nq; ++j) {
@@ -168,7 +193,7 @@ void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm
         d.sval = R.sval;
         d.S = R.S;
         d.N = R.N;
-        d.parts = stage_parts(R.S);
+        d.parts = spread ? EVAL_WAVES : stage_parts(R.S);
         const int64_t groups = cdiv(cdiv(R.N, TILE_ROWS), EVAL_WAVES / d.parts);
         d.task0 = (int32_t)task;
         d.ntasks = (int32_t)std::max<int64_t>(1, cdiv(groups, gpt));
@@ -184,6 +209,7 @@ void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm
     h->nrows = hoist ? (int32_t)row : 0;
     h->k = k;
     h->gpt = gpt;
+    h->spread = spread;
     h->clk_out = clk_out;
 }
 

@@ -448,6 +448,47 @@ struct GroupShared {
     uint4 xs[EVAL_WAVES][TILE_ROWS * FS * 2 / 16];
 };
 
+// Where a wave keeps the 32 costs of its j-th stage in a spread group: the part
+// of its slice of u past the hoisted rows that it can have.
+constexpr int SPREAD_STAGES = 2 * CM_STAGE_CHUNK;
+static_assert(SPREAD_STAGES / EVAL_WAVES * 2 == USTAGE && TILE_ROWS == H, "halves of the slice");
+__device__ inline float *spread_cost(GroupShared &sh, int wave, int j)
+{
+    return reinterpret_cast<float *>(&sh.u[wave][(USTAGE / 2 + j) * (H / 4)]);
+}
+
+// The chains of a spread group: part p of P holds the stages of waves
+// 8p / P .. 8 (p + 1) / P - 1, which one thread per (part, candidate) adds in
+// ascending order; the parts are combined as in eval_group.  Every thread of
+// the workgroup calls this.
+template <bool kShared>
+__device__ __forceinline__ void spread_sum(int S, int P, int tile, int N, float *cost,
+                                           GroupShared &sh)
+{
+    const int tid = threadIdx.x, n = tid % TILE_ROWS, p = tid / TILE_ROWS;
+    float sum = 0.f, comp = 0.f;
+    if (p < P) {
+        const int share = EVAL_WAVES / P;
+        for (int w = p * share; w < (p + 1) * share; ++w) {
+            const int m = (S * (w + 1)) / EVAL_WAVES - (S * w) / EVAL_WAVES;
+            for (int j = 0; j < m; ++j) kahan_add(sum, comp, spread_cost(sh, w, j)[n]);
+        }
+        if (P > 1) sh.part[p][n] = make_float2(sum, comp);
+    }
+    if (P > 1) __syncthreads();
+    const int i = tile * TILE_ROWS + n;
+    if (p == 0 && i < N) {
+        float A = 0.f, B = 0.f;
+        for (int r = 0; r < P; ++r) {
+            const float2 pc = P > 1 ? sh.part[r][n] : make_float2(sum, comp);
+            kahan_add(A, B, pc.x);
+            kahan_add(A, B, -pc.y);
+        }
+        if (kShared) store_shared(cost + i, A - B);
+        else cost[i] = A - B;
+    }
+}
+
 typedef __attribute__((address_space(3))) void lds_void;
 // Views of a copy block in other element types (may_alias: no type-based
 // alias analysis between them and the block's own type).
@@ -484,12 +525,16 @@ static_assert(TILE_ROWS * FS * 2 == 2560, "three copies of 1,024 + 1,024 + 512 b
 // every stage's cost to Q.stage[s][i].  kIndexed: the feature row of (s, i)
 // is row Q.ridx[s][i] of the table Q.x (memoized rows); a row number outside
 // the table makes that stage's cost NaN.
-template <bool kShared, bool kStage = false, bool kIndexed = false>
+// kSpread (a query of at most SPREAD_STAGES stages): the group is one tile
+// whose stages all EVAL_WAVES waves share; the Q.P chains of additions are
+// walked over the stage costs in LDS afterwards, in the same order.
+template <bool kShared, bool kStage = false, bool kIndexed = false, bool kSpread = false>
 __device__ __forceinline__ void eval_group(const QueryView &Q, int group, int wave, int lane,
                                            const Weights &w, const Pairs &kp,
                                            const uint32_t *tab, GroupShared &sh)
 {
-    const int P = Q.P;
+    static_assert(!kSpread || (!kStage && !kIndexed), "not written");
+    const int P = kSpread ? EVAL_WAVES : Q.P;  // waves that share a tile
     const int tile = group * (EVAL_WAVES / P) + wave / P;
     const int part = wave % P;
     // lane l: g = l / 16 selects the features and hoisted units it feeds to
@@ -595,6 +640,7 @@ __device__ __forceinline__ void eval_group(const QueryView &Q, int group, int wa
             asm volatile("" ::: "memory");
             const float va = stage_math(in, u, upper, w, kp, tab, sum, comp);
             if (kStage && q == 0 && valid) Q.stage[(int64_t)s * Q.N + i] = va;
+            if (kSpread && q == 0) spread_cost(sh, wave, s - s0)[n] = va;
             if (s + 1 >= s1) break;
 
             if ((s + 1 - s0) % USTAGE == 0) refill_u(ur, ug, s + 1, min(USTAGE, s1 - s - 1), lane);
@@ -609,6 +655,7 @@ __device__ __forceinline__ void eval_group(const QueryView &Q, int group, int wa
             asm volatile("" ::: "memory");
             const float vb = stage_math(in, u, upper, w, kp, tab, sum, comp);
             if (kStage && q == 0 && valid) Q.stage[(int64_t)(s + 1) * Q.N + i] = vb;
+            if (kSpread && q == 0) spread_cost(sh, wave, s + 1 - s0)[n] = vb;
         }
     }
     if (kIndexed && s0 < s1) {
@@ -666,6 +713,12 @@ __device__ __forceinline__ void eval_group(const QueryView &Q, int group, int wa
             const float vb = stage_math(B, u, upper, w, kp, tab, sum, comp);
             if (kStage && q == 0 && valid) Q.stage[(int64_t)(s + 1) * Q.N + i] = vb;
         }
+    }
+
+    if (kSpread) {
+        __syncthreads();
+        spread_sum<kShared>(Q.S, Q.P, tile, Q.N, Q.cost, sh);
+        return;
     }
 
     // combine the parts of each tile in ascending order

@@ -152,11 +152,12 @@ __device__ __forceinline__ float stage_math8(const StageIn8 &in, const float4 *u
 // eval_group of the FP8 form (see eval_bf16.h for the work split).  Q.x
 // points at the query's code bytes [S][N][40], or with kIndexed at a table of
 // code rows that Q.ridx[s][i] numbers (memoized rows).
-template <bool kShared, bool kStage = false, bool kIndexed = false>
+template <bool kShared, bool kStage = false, bool kIndexed = false, bool kSpread = false>
 __device__ __forceinline__ void eval_group8(const QueryView8 &Q, int group, int wave, int lane,
                                             const Weights8 &w, bf16eval::GroupShared &sh)
 {
-    const int P = Q.P;
+    static_assert(!kSpread || (!kStage && !kIndexed), "not written");
+    const int P = kSpread ? EVAL_WAVES : Q.P;  // waves that share a tile
     const int tile = group * (EVAL_WAVES / P) + wave / P;
     const int part = wave % P;
     const int n = lane & 31;
@@ -223,7 +224,8 @@ __device__ __forceinline__ void eval_group8(const QueryView8 &Q, int group, int 
             const int c1 = min(c0 + U8, s1);
             refill_u(ur, ug, c0, c1 - c0, lane);
             auto stage = [&](const StageIn8 &x, int s) {
-                stage_math8(x, ur + (s - c0) * (H / 4), hf, w, sum, comp);
+                const float v = stage_math8(x, ur + (s - c0) * (H / 4), hf, w, sum, comp);
+                if (kSpread && hf == 0) bf16eval::spread_cost(sh, wave, s - s0)[n] = v;
             };
             if (c0 == s0) {
                 load_next(in[0]);
@@ -292,6 +294,11 @@ __device__ __forceinline__ void eval_group8(const QueryView8 &Q, int group, int 
         }
     }
 
+    if (kSpread) {
+        __syncthreads();
+        bf16eval::spread_sum<kShared>(Q.S, Q.P, tile, Q.N, Q.cost, sh);
+        return;
+    }
     if (P > 1) {
         if (hf == 0) sh.part[wave][n] = make_float2(sum, comp);
         __syncthreads();

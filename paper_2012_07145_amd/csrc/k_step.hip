@@ -60,6 +60,7 @@ __device__ __forceinline__ void select_tile(const StepQ &D, int q, int tile, int
 }
 
 // One task's evaluation: gpt row-tile groups of one query.
+template <bool kSpread>
 __device__ __forceinline__ void eval_task(const StepQ &D, int tq, int gpt, int wave, int lane,
                                           const Bf16Pack *__restrict__ pk, const Pairs &kp,
                                           const uint32_t *tab, GroupShared &gsh)
@@ -71,17 +72,21 @@ __device__ __forceinline__ void eval_task(const StepQ &D, int tq, int gpt, int w
     Q.cost = D.cost;
     Q.S = D.S;
     Q.N = D.N;
-    Q.P = D.parts;
-    const int group_rows = TILE_ROWS * (EVAL_WAVES / Q.P);
+    Q.P = stage_parts(D.S);
+    const int group_rows = TILE_ROWS * (EVAL_WAVES / D.parts);
     const Weights w = load_weights(pk, lane);
     for (int g = 0; g < gpt; ++g) {
         const int group = tq * gpt + g;
         if (group * group_rows >= Q.N) break;  // uniform
-        eval_group<true>(Q, group, wave, lane, w, kp, tab, gsh);
+        if (kSpread && Q.P < D.parts)
+            eval_group<true, false, false, true>(Q, group, wave, lane, w, kp, tab, gsh);
+        else
+            eval_group<true>(Q, group, wave, lane, w, kp, tab, gsh);
         __syncthreads();  // the group's LDS is reused by the next group
     }
 }
 
+template <bool kSpread>
 __device__ __forceinline__ void eval_task(const StepQ &D, int tq, int gpt, int wave, int lane,
                                           const Fp8Pack *__restrict__ pk, const Pairs &,
                                           const uint32_t *, GroupShared &gsh)
@@ -93,13 +98,16 @@ __device__ __forceinline__ void eval_task(const StepQ &D, int tq, int gpt, int w
     Q.cost = D.cost;
     Q.S = D.S;
     Q.N = D.N;
-    Q.P = D.parts;
-    const int group_rows = TILE_ROWS * (EVAL_WAVES / Q.P);
+    Q.P = stage_parts(D.S);
+    const int group_rows = TILE_ROWS * (EVAL_WAVES / D.parts);
     const fp8eval::Weights8 w = fp8eval::load_weights8(pk, lane);
     for (int g = 0; g < gpt; ++g) {
         const int group = tq * gpt + g;
         if (group * group_rows >= Q.N) break;  // uniform
-        fp8eval::eval_group8<true>(Q, group, wave, lane, w, gsh);
+        if (kSpread && Q.P < D.parts)
+            fp8eval::eval_group8<true, false, false, true>(Q, group, wave, lane, w, gsh);
+        else
+            fp8eval::eval_group8<true>(Q, group, wave, lane, w, gsh);
         __syncthreads();
     }
 }
@@ -115,7 +123,7 @@ union StepShared {
     TopkShared<NT> t;
 };
 
-template <class Pack>
+template <bool kSpread, class Pack>
 __device__ __forceinline__ void step_body(const StepHead *__restrict__ h,
                                           const StepQ *__restrict__ qs, uint32_t *ctl,
                                           uint64_t *tpart, const Pack *__restrict__ pk)
@@ -158,7 +166,7 @@ __device__ __forceinline__ void step_body(const StepHead *__restrict__ h,
         const StepQ &D = qs[q];
         const int tq = t - D.task0;  // task within the query
         const int group_rows = TILE_ROWS * (EVAL_WAVES / D.parts);
-        eval_task(D, tq, gpt, wave, lane, pk, kp, tab, gsh);
+        eval_task<kSpread>(D, tq, gpt, wave, lane, pk, kp, tab, gsh);
         // this task's costs (coherent stores) have completed before it counts
         // itself at its selection tile; the next task is taken only now, so
         // that the queue hands work to whichever workgroup is free first
@@ -211,26 +219,38 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
     const StepHead *__restrict__ h, const StepQ *__restrict__ qs, uint32_t *ctl,
     uint64_t *tpart, const Bf16Pack *__restrict__ pk)
 {
-    step_body(h, qs, ctl, tpart, pk);
+    step_body<false>(h, qs, ctl, tpart, pk);
 }
 
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_step_fp8(
     const StepHead *__restrict__ h, const StepQ *__restrict__ qs, uint32_t *ctl,
     uint64_t *tpart, const Fp8Pack *__restrict__ pk)
 {
-    step_body(h, qs, ctl, tpart, pk);
+    step_body<false>(h, qs, ctl, tpart, pk);
 }
 
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 k_step_bf16_value(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Bf16Pack *__restrict__ pk)
 {
-    step_body(&a.h, a.q, ctl, tpart, pk);
+    step_body<false>(&a.h, a.q, ctl, tpart, pk);
+}
+
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+k_step_bf16_spread(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Bf16Pack *__restrict__ pk)
+{
+    step_body<true>(&a.h, a.q, ctl, tpart, pk);
 }
 
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
 k_step_fp8_value(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Fp8Pack *__restrict__ pk)
 {
-    step_body(&a.h, a.q, ctl, tpart, pk);
+    step_body<false>(&a.h, a.q, ctl, tpart, pk);
+}
+
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
+k_step_fp8_spread(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Fp8Pack *__restrict__ pk)
+{
+    step_body<true>(&a.h, a.q, ctl, tpart, pk);
 }
 
 }  // namespace
@@ -251,10 +271,11 @@ hipError_t launch_step(const StepArgs &a, uint32_t *ctl, uint64_t *tpart, const 
 {
     grid = std::min(grid, a.h.ntasks);  // a workgroup without a task would only leave
     if (prec == CM_FP8)
-        hipLaunchKernelGGL(k_step_fp8_value, dim3(grid), dim3(NT), 0, st, a, ctl, tpart, m.d_fp8);
+        hipLaunchKernelGGL(a.h.spread ? k_step_fp8_spread : k_step_fp8_value, dim3(grid), dim3(NT),
+                           0, st, a, ctl, tpart, m.d_fp8);
     else
-        hipLaunchKernelGGL(k_step_bf16_value, dim3(grid), dim3(NT), 0, st, a, ctl, tpart,
-                           &m.d->bf16);
+        hipLaunchKernelGGL(a.h.spread ? k_step_bf16_spread : k_step_bf16_value, dim3(grid),
+                           dim3(NT), 0, st, a, ctl, tpart, &m.d->bf16);
     return hipGetLastError();
 }
 

@@ -87,3 +87,33 @@ def test_step_by_value_and_by_block(cm, model, prec, graph):
             cm.cm_step_run(step, batch, rows, K, *got)
             _same(got, want, batch.n_cands)
     step.close()
+
+
+SPREAD_SHAPES = [
+    [(5, 1)], [(8, 31)], [(16, 32)], [(17, 33)], [(32, 200)], [(33, 8192)], [(64, 8193)],
+    [(64, 257)], [(65, 40)], [(20, 4100), (3, 60), (64, 0), (120, 33)], [(9, 0)],
+    [(7 + 4 * j, 17 * j) for j in range(15)],
+]
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+@pytest.mark.parametrize("shapes", SPREAD_SHAPES, ids=lambda s: "x".join(map(str, s[0])))
+def test_small_batches_spread_over_the_waves(cm, model, prec, shapes):
+    """Batches of few row tiles, whose stages all waves of a workgroup share: the
+    bits of the per-call path at the edges of the stage split, of the tiles and
+    of the rule (256 tiles), beside queries that are not spread, and with
+    several tiles per task."""
+    import torch
+    rng = np.random.default_rng(77)
+    queries = [draw_query(rng, S, N) for S, N in shapes]
+    batch = _pack(cm, prec, queries)
+    want = _per_call(cm, model, prec, batch, queries)
+    step = cm.cm_step_create(model, prec, max_queries=len(queries),
+                             max_stages=sum(S for S, _ in shapes),
+                             max_cands=max(1, sum(N for _, N in shapes)), max_k=K, slots=2)
+    for tiles in (1, 2, 8):
+        cm.cm_step_set_config(step, 0, tiles, 1)
+        got = _outs(batch)
+        cm.cm_step_run(step, batch, None, K, *got)
+        _same(got, want, batch.n_cands)
+    step.close()
