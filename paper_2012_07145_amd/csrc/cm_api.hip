@@ -375,6 +375,21 @@ cm_status cm_model_create(const cm_model_desc *d, const float *params, cm_model 
             if (m < C) w[32 + t] = W2[m * H + 4 * t + g];
         for (int v = 0; v < 10; ++v) std::memcpy(&p32.w[v][lane], w + 4 * v, 16);
     }
+    HoistPack &ph = md.hoist;
+    for (int lane = 0; lane < 64; ++lane) {
+        const int m = lane & 15, g = lane >> 4;
+        float w[40] = {};
+        for (int hh = 0; hh < 2; ++hh) {
+            const int row = 16 * hh + m;
+            for (int t = 0; t < 14; ++t)
+                if (row < E) w[14 * hh + t] = params[OFF_WP + row * FP + 4 * t + g];
+            for (int t = 0; t < 6; ++t) w[28 + 6 * hh + t] = W1[row * 2 * E + 4 * t + g];
+        }
+        for (int v = 0; v < 10; ++v) std::memcpy(&ph.w[v][lane], w + 4 * v, 16);
+    }
+    std::memcpy(ph.bp, params + OFF_BP, E * sizeof(float));
+    std::memcpy(ph.b1, params + OFF_B1, H * sizeof(float));
+    std::memcpy(ph.beta, md.beta, H * sizeof(float));
     static const LogTable log_table;
     std::memcpy(p32.log, log_table.e, sizeof(p32.log));
     std::memcpy(p32.bs, bs, E * sizeof(float));

@@ -40,6 +40,16 @@ __host__ __device__ constexpr int stage_parts(int S)
 {
     return S <= CM_STAGE_CHUNK / 2 ? 1 : S <= CM_STAGE_CHUNK ? 2 : S <= 2 * CM_STAGE_CHUNK ? 4 : 8;
 }
+
+// A small step's waves share each tile's stages (queries of at most
+// SPREAD_STAGES stages, those of fewer than 8 parts) and hoist their own, up to
+// 4 a wave, where no query has more than OWN_HOIST_STAGES: 20 x 200 takes 20.8
+// us with a hoist kernel before the step and 18.7 us so, in FP8 19.5 and 17.2,
+// 32 x 200 22.1 and 20.1; with 8 a wave, 64 x 200 took 25.7 and 25.4 us and 64 x
+// 8,000 in FP8 27.7 and 28.3.
+constexpr int SPREAD_STAGES = 2 * CM_STAGE_CHUNK;
+constexpr int OWN_HOIST_STAGES = 4 * EVAL_WAVES;
+
 constexpr int TOPK_TILE = 4096;     // candidates per selection tile of the step kernel
 constexpr int TOPK_CALL_TILE = 16384; // candidates per tile of the selection kernel
 
@@ -103,13 +113,25 @@ struct Fp8Pack {
 
 // Everything a model holds on the device from its creation, filled by one
 // copy (the log table by a kernel after it).
+// Operands of the hoist on the float32 matrix cores, laid out like Fp32Pack:
+// values 0..27: W_p rows 0..15 (14 steps), then 16..23; 28..39: W_1[:, :24]
+// rows 0..15 (6 steps), then 16..31.
+struct HoistPack {
+    float4 w[10][64];
+    float4 bp[8];  // b_p, zeros past 24
+    float4 b1[8];
+    float4 beta[8];
+};
+
 struct ModelData {
     float params[N_PARAMS];  // float32 blob as given
     float beta[H];           // W_1[:, 24:] b_s, added when folding
+    HoistPack hoist;         // packed operands of the steps' own hoist
     Fp32Pack fp32;           // packed operands of the float32 evaluator
     Bf16Pack bf16;           // packed operands of the bf16 evaluator
 };
-static_assert(offsetof(ModelData, fp32) % 16 == 0 && offsetof(ModelData, bf16) % 16 == 0,
+static_assert(offsetof(ModelData, hoist) % 16 == 0 && offsetof(ModelData, fp32) % 16 == 0 &&
+                  offsetof(ModelData, bf16) % 16 == 0,
               "operands are read in 16-byte units");
 
 struct Model {
@@ -225,7 +247,8 @@ struct StepHead {
     int32_t nrows;     // hoist rows over all queries
     int32_t k;         // beam width
     int32_t gpt;       // row-tile groups per task (1, 2 or 4)
-    int32_t spread;    // tiles of queries of up to SPREAD_STAGES stages take all waves
+    int32_t spread;    // 1: tiles of queries of up to SPREAD_STAGES stages take all waves;
+                       // 2: and their waves hoist their own stages (no longer query)
     // where the launch's (first start, last end) clock pair also goes, or
     // null: host memory mapped for the device, so a server learns it without
     // a copy

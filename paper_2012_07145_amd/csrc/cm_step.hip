@@ -178,8 +178,10 @@ void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm
     const bool spread = spread_pays(r, nq, S.cus);
     std::memset(h, 0, sizeof *h);
     int64_t task = 0, row = 0, tile = 0;
+    int32_t longest = 0;  // stages
     for (int j = 0; j < nq; ++j) {
         const StepReq &R = r[order[j]];
+        longest = std::max(longest, R.S);
         StepQ &d = qs[j];
         std::memset(&d, 0, sizeof d);
         d.x = R.x;
@@ -206,10 +208,11 @@ void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm
     }
     h->nq = nq;
     h->ntasks = (int32_t)task;
-    h->nrows = hoist ? (int32_t)row : 0;
+    const bool own = spread && hoist && longest <= OWN_HOIST_STAGES;
+    h->nrows = hoist && !own ? (int32_t)row : 0;
     h->k = k;
     h->gpt = gpt;
-    h->spread = spread;
+    h->spread = own ? 2 : spread;
     h->clk_out = clk_out;
 }
 

@@ -45,6 +45,7 @@
 #pragma once
 
 #include "cm_internal.h"
+#include "hoist_dev.h"
 
 namespace cm {
 namespace bf16eval {
@@ -437,6 +438,10 @@ struct QueryView {
     const int32_t *ridx;  // memoized rows: row numbers [S][N] into x (only with kIndexed)
     uint32_t rows;        // rows in the table x (only with kIndexed)
     int S, N, P;
+    // spread groups that hoist their own stages: algorithm features [S][56]
+    // (null: u is given), operands and scale
+    const float *pipe = nullptr;
+    const HoistPack *hoist = nullptr;
 };
 
 // LDS of one group of EVAL_WAVES waves.
@@ -450,11 +455,21 @@ struct GroupShared {
 
 // Where a wave keeps the 32 costs of its j-th stage in a spread group: the part
 // of its slice of u past the hoisted rows that it can have.
-constexpr int SPREAD_STAGES = 2 * CM_STAGE_CHUNK;
 static_assert(SPREAD_STAGES / EVAL_WAVES * 2 == USTAGE && TILE_ROWS == H, "halves of the slice");
 __device__ inline float *spread_cost(GroupShared &sh, int wave, int j)
 {
     return reinterpret_cast<float *>(&sh.u[wave][(USTAGE / 2 + j) * (H / 4)]);
+}
+
+// The hoisted rows of a spread wave's stages [s0, s1), at most hoist::ROWS, into
+// its slice from the algorithm features.
+static_assert(hoist::PASSES * 64 <= USTAGE * H, "fits the slice");
+__device__ __forceinline__ void own_rows(float4 *ur, const float *pipe, const HoistPack *pk,
+                                         float scale, int s0, int s1, int lane)
+{
+    float v[hoist::PASSES];
+    hoist::load_pipe(v, pipe + (int64_t)s0 * FP, s1 - s0, lane);
+    hoist::hoist_rows(pk, v, s1 - s0, scale, reinterpret_cast<float *>(ur), lane);
 }
 
 // The chains of a spread group: part p of P holds the stages of waves
@@ -625,8 +640,13 @@ __device__ __forceinline__ void eval_group(const QueryView &Q, int group, int wa
         // the terms go first: waiting for a stage's copy then covers them
         load_t(tA);
         dma_rows(xsw, xr, row0, xsoff, lane);
+        if (kSpread) {
+            if (Q.pipe) own_rows(ur, Q.pipe, Q.hoist, 1.f, s0, s1, lane);
+            else refill_u(ur, ug, s0, s1 - s0, lane);
+        }
         for (int s = s0; s < s1; s += 2) {
-            if ((s - s0) % USTAGE == 0) refill_u(ur, ug, s, min(USTAGE, s1 - s), lane);
+            if (!kSpread && (s - s0) % USTAGE == 0)
+                refill_u(ur, ug, s, min(USTAGE, s1 - s), lane);
             StageIn in;
             float4 u[2];
             read_u(u, ur + ((s - s0) % USTAGE) * (H / 4), g);
@@ -643,7 +663,8 @@ __device__ __forceinline__ void eval_group(const QueryView &Q, int group, int wa
             if (kSpread && q == 0) spread_cost(sh, wave, s - s0)[n] = va;
             if (s + 1 >= s1) break;
 
-            if ((s + 1 - s0) % USTAGE == 0) refill_u(ur, ug, s + 1, min(USTAGE, s1 - s - 1), lane);
+            if (!kSpread && (s + 1 - s0) % USTAGE == 0)
+                refill_u(ur, ug, s + 1, min(USTAGE, s1 - s - 1), lane);
             read_u(u, ur + ((s + 1 - s0) % USTAGE) * (H / 4), g);
             stage_in(in, tB);
             if (s + 2 < s1) {

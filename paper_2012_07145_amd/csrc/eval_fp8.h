@@ -49,6 +49,9 @@ struct QueryView8 {
     const int32_t *ridx;  // memoized rows: row numbers [S][N] into x (only with kIndexed)
     uint32_t rows;        // rows in the table x (only with kIndexed)
     int S, N, P;
+    const float *pipe = nullptr;  // as in bf16eval::QueryView
+    const HoistPack *hoist = nullptr;
+    float uh = 1.f;               // s_h
 };
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -222,7 +225,8 @@ __device__ __forceinline__ void eval_group8(const QueryView8 &Q, int group, int 
         constexpr int U8 = USTAGE / 3 * 3;
         for (int c0 = s0; c0 < s1; c0 += U8) {
             const int c1 = min(c0 + U8, s1);
-            refill_u(ur, ug, c0, c1 - c0, lane);
+            const bool own = kSpread && Q.pipe;  // its one chunk's rows are hoisted below
+            if (!own) refill_u(ur, ug, c0, c1 - c0, lane);
             auto stage = [&](const StageIn8 &x, int s) {
                 const float v = stage_math8(x, ur + (s - c0) * (H / 4), hf, w, sum, comp);
                 if (kSpread && hf == 0) bf16eval::spread_cost(sh, wave, s - s0)[n] = v;
@@ -232,6 +236,7 @@ __device__ __forceinline__ void eval_group8(const QueryView8 &Q, int group, int 
                 asm volatile("" ::: "memory");
                 load_next(in[1]);
             }
+            if (own) bf16eval::own_rows(ur, Q.pipe, Q.hoist, Q.uh, s0, s1, lane);
             int s = c0;
             for (; s + 3 <= c1; s += 3) {
 #pragma unroll

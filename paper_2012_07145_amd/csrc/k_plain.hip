@@ -15,9 +15,12 @@
 #include <algorithm>
 
 #include "cm_internal.h"
+#include "hoist_dev.h"
 
 namespace cm {
 namespace {
+
+using namespace hoist;
 
 // One stage row of the hoist by a 64-thread workgroup: p = the stage's 56
 // algorithm features, u = its 32 output floats.
@@ -112,7 +115,6 @@ __global__ __launch_bounds__(64) void k_hoist_step_value(StepArgs a,
 // over a million sums, subnormal ones included).  So the layers stay
 // unfolded: bs + Ws x, then u + W1 es, then b2 + W2 h.
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 
 // Packed operands of the first layer held by a lane for the whole launch (lane
@@ -140,40 +142,6 @@ __device__ inline Fp32Weights load_fp32(const Fp32Pack *__restrict__ pk, int lan
     W.bs[1] = f32x4{s1.x, s1.y, s1.z, s1.w};
     W.b2 = f32x4{s2.x, s2.y, s2.z, s2.w};
     return W;
-}
-
-__device__ inline f32x4 mfma4(float a, float b, f32x4 c)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
-
-__device__ inline void swap32(float &a, float &b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                    false);
-    a = __uint_as_float(r[0]);
-    b = __uint_as_float(r[1]);
-}
-
-__device__ inline void swap16(float &a, float &b)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false,
-                                                    false);
-    a = __uint_as_float(r[0]);
-    b = __uint_as_float(r[1]);
-}
-
-// A layer's output tile (lane group g = lane / 16 holds rows 4g .. 4g+3 of
-// its column) as the next layer's operands: step t's operand is row 4t + g,
-// the transpose of the 4 x 4 (group, register) grid.
-__device__ inline void transpose4(f32x4 &v)
-{
-    float a = v[0], b = v[1], c = v[2], d = v[3];
-    swap32(a, c);
-    swap32(b, d);
-    swap16(a, b);
-    swap16(c, d);
-    v = f32x4{a, b, c, d};
 }
 
 __device__ inline float relu32(float a) { return a < 0.f ? 0.f : a; }  // a NaN passes through

@@ -63,7 +63,8 @@ __device__ __forceinline__ void select_tile(const StepQ &D, int q, int tile, int
 template <bool kSpread>
 __device__ __forceinline__ void eval_task(const StepQ &D, int tq, int gpt, int wave, int lane,
                                           const Bf16Pack *__restrict__ pk, const Pairs &kp,
-                                          const uint32_t *tab, GroupShared &gsh)
+                                          const uint32_t *tab, GroupShared &gsh,
+                                          const HoistPack *hp)
 {
     QueryView Q;
     Q.x = static_cast<const uint16_t *>(D.x);
@@ -74,6 +75,10 @@ __device__ __forceinline__ void eval_task(const StepQ &D, int tq, int gpt, int w
     Q.N = D.N;
     Q.P = stage_parts(D.S);
     const int group_rows = TILE_ROWS * (EVAL_WAVES / D.parts);
+    if (hp) {
+        Q.pipe = D.pipe;
+        Q.hoist = hp;
+    }
     const Weights w = load_weights(pk, lane);
     for (int g = 0; g < gpt; ++g) {
         const int group = tq * gpt + g;
@@ -89,7 +94,8 @@ __device__ __forceinline__ void eval_task(const StepQ &D, int tq, int gpt, int w
 template <bool kSpread>
 __device__ __forceinline__ void eval_task(const StepQ &D, int tq, int gpt, int wave, int lane,
                                           const Fp8Pack *__restrict__ pk, const Pairs &,
-                                          const uint32_t *, GroupShared &gsh)
+                                          const uint32_t *, GroupShared &gsh,
+                                          const HoistPack *hp)
 {
     fp8eval::QueryView8 Q;
     Q.x = static_cast<const uint8_t *>(D.x);
@@ -100,6 +106,11 @@ __device__ __forceinline__ void eval_task(const StepQ &D, int tq, int gpt, int w
     Q.N = D.N;
     Q.P = stage_parts(D.S);
     const int group_rows = TILE_ROWS * (EVAL_WAVES / D.parts);
+    if (hp) {
+        Q.pipe = D.pipe;
+        Q.hoist = hp;
+        Q.uh = pk->uh;
+    }
     const fp8eval::Weights8 w = fp8eval::load_weights8(pk, lane);
     for (int g = 0; g < gpt; ++g) {
         const int group = tq * gpt + g;
@@ -123,10 +134,11 @@ union StepShared {
     TopkShared<NT> t;
 };
 
-template <bool kSpread, class Pack>
+template <bool kSpread, bool kOwn = false, class Pack>
 __device__ __forceinline__ void step_body(const StepHead *__restrict__ h,
                                           const StepQ *__restrict__ qs, uint32_t *ctl,
-                                          uint64_t *tpart, const Pack *__restrict__ pk)
+                                          uint64_t *tpart, const Pack *__restrict__ pk,
+                                          const HoistPack *__restrict__ hp = nullptr)
 {
     __shared__ StepShared ssh;
     __shared__ uint32_t tab[LogTable<Pack>::n];
@@ -166,7 +178,7 @@ __device__ __forceinline__ void step_body(const StepHead *__restrict__ h,
         const StepQ &D = qs[q];
         const int tq = t - D.task0;  // task within the query
         const int group_rows = TILE_ROWS * (EVAL_WAVES / D.parts);
-        eval_task<kSpread>(D, tq, gpt, wave, lane, pk, kp, tab, gsh);
+        eval_task<kSpread>(D, tq, gpt, wave, lane, pk, kp, tab, gsh, kOwn ? hp : nullptr);
         // this task's costs (coherent stores) have completed before it counts
         // itself at its selection tile; the next task is taken only now, so
         // that the queue hands work to whichever workgroup is free first
@@ -235,10 +247,14 @@ k_step_bf16_value(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Bf16Pack *__
     step_body<false>(&a.h, a.q, ctl, tpart, pk);
 }
 
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
-k_step_bf16_spread(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Bf16Pack *__restrict__ pk)
+// A spread step has at most one workgroup per compute unit, so its waves may
+// hold twice the registers where they need them.
+template <bool kOwn>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2, 2))) void
+k_step_bf16_spread(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Bf16Pack *__restrict__ pk,
+                   const HoistPack *__restrict__ hp)
 {
-    step_body<true>(&a.h, a.q, ctl, tpart, pk);
+    step_body<true, kOwn>(&a.h, a.q, ctl, tpart, pk, hp);
 }
 
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
@@ -247,10 +263,13 @@ k_step_fp8_value(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Fp8Pack *__re
     step_body<false>(&a.h, a.q, ctl, tpart, pk);
 }
 
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4, 4))) void
-k_step_fp8_spread(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Fp8Pack *__restrict__ pk)
+template <bool kOwn>
+__global__ __launch_bounds__(NT)
+__attribute__((amdgpu_waves_per_eu(kOwn ? 2 : 4, kOwn ? 2 : 4))) void
+k_step_fp8_spread(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Fp8Pack *__restrict__ pk,
+                  const HoistPack *__restrict__ hp)
 {
-    step_body<true>(&a.h, a.q, ctl, tpart, pk);
+    step_body<true, kOwn>(&a.h, a.q, ctl, tpart, pk, hp);
 }
 
 }  // namespace
@@ -270,12 +289,18 @@ hipError_t launch_step(const StepArgs &a, uint32_t *ctl, uint64_t *tpart, const 
                        cm_precision prec, int grid, hipStream_t st)
 {
     grid = std::min(grid, a.h.ntasks);  // a workgroup without a task would only leave
-    if (prec == CM_FP8)
-        hipLaunchKernelGGL(a.h.spread ? k_step_fp8_spread : k_step_fp8_value, dim3(grid), dim3(NT),
-                           0, st, a, ctl, tpart, m.d_fp8);
+    const bool own = a.h.spread == 2;
+    if (prec == CM_FP8 && a.h.spread)
+        hipLaunchKernelGGL(own ? k_step_fp8_spread<true> : k_step_fp8_spread<false>, dim3(grid),
+                           dim3(NT), 0, st, a, ctl, tpart, m.d_fp8, &m.d->hoist);
+    else if (prec == CM_FP8)
+        hipLaunchKernelGGL(k_step_fp8_value, dim3(grid), dim3(NT), 0, st, a, ctl, tpart, m.d_fp8);
+    else if (a.h.spread)
+        hipLaunchKernelGGL(own ? k_step_bf16_spread<true> : k_step_bf16_spread<false>, dim3(grid),
+                           dim3(NT), 0, st, a, ctl, tpart, &m.d->bf16, &m.d->hoist);
     else
-        hipLaunchKernelGGL(a.h.spread ? k_step_bf16_spread : k_step_bf16_value, dim3(grid),
-                           dim3(NT), 0, st, a, ctl, tpart, &m.d->bf16);
+        hipLaunchKernelGGL(k_step_bf16_value, dim3(grid), dim3(NT), 0, st, a, ctl, tpart,
+                           &m.d->bf16);
     return hipGetLastError();
 }
 
