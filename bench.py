@@ -45,7 +45,8 @@ SESSIONS = 256
 # header's constants (the stage split among them) shape its work too, so its
 # "#define CM_" lines join the hash (its comments do not)
 STEP_SOURCES = tuple("paper_2012_07145_amd/csrc/" + f for f in
-                     ("k_step.hip", "eval_bf16.h", "eval_fp8.h", "topk_dev.h", "cm_internal.h"))
+                     ("k_step.hip", "eval_bf16.h", "eval_fp8.h", "hoist_dev.h", "topk_dev.h",
+                      "cm_internal.h"))
 STEP_HEADER = "include/cm.h"
 
 
