@@ -164,13 +164,37 @@ struct EvalQ {
     int64_t stage_off; // offset (floats) of this query's per-stage costs [S][N] (terms_off / 8)
 };
 
-struct EvalLaunch {
+// The descriptors go to the kernels by value.  Their arguments are copied at
+// every launch, 2.6 KB of them for QMAX queries in 4.4 us of the caller's time
+// and 0.7 KB in 3.0, so a launch of up to QFEW queries passes only so many.
+template <int Q> struct EvalLaunchOf {
     int32_t nq;
     int32_t ntasks;    // row-tile groups (bf16, FP8) or tiles (fp32)
     int32_t nstages;   // hoist blocks
     int32_t pad;
-    EvalQ q[QMAX];
+    EvalQ q[Q];
 };
+typedef EvalLaunchOf<QMAX> EvalLaunch;
+constexpr int QFEW = 8;
+
+// Launches one of a kernel's two forms with the descriptors in L.
+template <class Few, class Many, class... A>
+inline hipError_t launch_eval(Few few, Many many, dim3 grid, dim3 block, hipStream_t st,
+                              const EvalLaunch &L, A... args)
+{
+    if (L.nq <= QFEW) {
+        EvalLaunchOf<QFEW> f;
+        f.nq = L.nq;
+        f.ntasks = L.ntasks;
+        f.nstages = L.nstages;
+        f.pad = 0;
+        for (int j = 0; j < QFEW; ++j) f.q[j] = L.q[j < L.nq ? j : 0];
+        hipLaunchKernelGGL(few, grid, block, 0, st, f, args...);
+    } else {
+        hipLaunchKernelGGL(many, grid, block, 0, st, L, args...);
+    }
+    return hipGetLastError();
+}
 
 struct FreezeQ {
     int32_t S, N;

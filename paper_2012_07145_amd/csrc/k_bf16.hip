@@ -9,9 +9,9 @@ namespace {
 
 using namespace bf16eval;
 
-template <bool kStage, bool kIndexed>
+template <bool kStage, bool kIndexed, int kQ>
 __global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_eval_bf16(
-    EvalLaunch L, const Bf16Pack *__restrict__ pk, const uint16_t *sched, const float *terms,
+    EvalLaunchOf<kQ> L, const Bf16Pack *__restrict__ pk, const uint16_t *sched, const float *terms,
     const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage,
     const int32_t *__restrict__ ridx, uint32_t rows)
 {
@@ -62,21 +62,14 @@ hipError_t launch_eval_bf16(const EvalLaunch &L, const Model &m, const uint16_t 
 {
     if (L.ntasks == 0) return hipSuccess;
     const dim3 g(L.ntasks), b(EVAL_WAVES * 64);
-    if (ridx) {
-        if (stage)
-            hipLaunchKernelGGL((k_eval_bf16<true, true>), g, b, 0, st, L, &m.d->bf16, sched, terms,
-                               U, cost, stage, ridx, rows);
-        else
-            hipLaunchKernelGGL((k_eval_bf16<false, true>), g, b, 0, st, L, &m.d->bf16, sched, terms,
-                               U, cost, stage, ridx, rows);
-    } else if (stage) {
-        hipLaunchKernelGGL((k_eval_bf16<true, false>), g, b, 0, st, L, &m.d->bf16, sched, terms, U,
-                           cost, stage, ridx, rows);
-    } else {
-        hipLaunchKernelGGL((k_eval_bf16<false, false>), g, b, 0, st, L, &m.d->bf16, sched, terms, U,
-                           cost, stage, ridx, rows);
-    }
-    return hipGetLastError();
+    auto go = [&](auto few, auto many) {
+        return launch_eval(few, many, g, b, st, L, &m.d->bf16, sched, terms, U, cost, stage, ridx,
+                           rows);
+    };
+    if (ridx && stage) return go(k_eval_bf16<true, true, QFEW>, k_eval_bf16<true, true, QMAX>);
+    if (ridx) return go(k_eval_bf16<false, true, QFEW>, k_eval_bf16<false, true, QMAX>);
+    if (stage) return go(k_eval_bf16<true, false, QFEW>, k_eval_bf16<true, false, QMAX>);
+    return go(k_eval_bf16<false, false, QFEW>, k_eval_bf16<false, false, QMAX>);
 }
 
 }  // namespace cm

@@ -11,9 +11,9 @@ namespace {
 
 using namespace fp8eval;
 
-template <bool kStage, bool kIndexed>
+template <bool kStage, bool kIndexed, int kQ>
 __global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_eval_fp8(
-    EvalLaunch L, const Fp8Pack *__restrict__ pk, const uint8_t *codes, const float *terms,
+    EvalLaunchOf<kQ> L, const Fp8Pack *__restrict__ pk, const uint8_t *codes, const float *terms,
     const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage,
     const int32_t *__restrict__ ridx, uint32_t rows)
 {
@@ -157,21 +157,14 @@ hipError_t launch_eval_fp8(const EvalLaunch &L, const Model &m, const uint8_t *c
 {
     if (L.ntasks == 0) return hipSuccess;
     const dim3 g(L.ntasks), b(EVAL_WAVES * 64);
-    if (ridx) {
-        if (stage)
-            hipLaunchKernelGGL((k_eval_fp8<true, true>), g, b, 0, st, L, m.d_fp8, codes, terms, U,
-                               cost, stage, ridx, rows);
-        else
-            hipLaunchKernelGGL((k_eval_fp8<false, true>), g, b, 0, st, L, m.d_fp8, codes, terms, U,
-                               cost, stage, ridx, rows);
-    } else if (stage) {
-        hipLaunchKernelGGL((k_eval_fp8<true, false>), g, b, 0, st, L, m.d_fp8, codes, terms, U,
-                           cost, stage, ridx, rows);
-    } else {
-        hipLaunchKernelGGL((k_eval_fp8<false, false>), g, b, 0, st, L, m.d_fp8, codes, terms, U,
-                           cost, stage, ridx, rows);
-    }
-    return hipGetLastError();
+    const Fp8Pack *pk = m.d_fp8;
+    auto go = [&](auto few, auto many) {
+        return launch_eval(few, many, g, b, st, L, pk, codes, terms, U, cost, stage, ridx, rows);
+    };
+    if (ridx && stage) return go(k_eval_fp8<true, true, QFEW>, k_eval_fp8<true, true, QMAX>);
+    if (ridx) return go(k_eval_fp8<false, true, QFEW>, k_eval_fp8<false, true, QMAX>);
+    if (stage) return go(k_eval_fp8<true, false, QFEW>, k_eval_fp8<true, false, QMAX>);
+    return go(k_eval_fp8<false, false, QFEW>, k_eval_fp8<false, false, QMAX>);
 }
 
 // x and codes must be 16-byte aligned (checked by the caller).

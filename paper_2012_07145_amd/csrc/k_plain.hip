@@ -48,7 +48,8 @@ __device__ inline void hoist_row(const float *__restrict__ params, const float *
     __syncthreads();  // lp and ep are reused by the next row
 }
 
-__global__ __launch_bounds__(64) void k_hoist(EvalLaunch L, const float *__restrict__ params,
+template <int kQ>
+__global__ __launch_bounds__(64) void k_hoist(EvalLaunchOf<kQ> L, const float *__restrict__ params,
                                               const float *__restrict__ beta, int fold,
                                               float scale, const float *__restrict__ pipe,
                                               float *__restrict__ U)
@@ -331,8 +332,9 @@ static_assert(FP32_TILE * F32_ROW == 2560, "three copies of 1,024 + 1,024 + 512 
 // (100 waves, each a serial walk over the stages), 42 us in tiles with log1pf
 // for every value, 31 us so; 4 x 64: 80, 6.5 and 6.0 us; 64 x 32,768 with its
 // selection: 304 us with log1pf, 201 us so.
+template <int kQ>
 __global__ __launch_bounds__(F32_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void
-k_eval_fp32(EvalLaunch L, const Fp32Pack *__restrict__ pk, const float *sched, const float *terms,
+k_eval_fp32(EvalLaunchOf<kQ> L, const Fp32Pack *__restrict__ pk, const float *sched, const float *terms,
             const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage)
 {
     __shared__ Fp32Shared sh;
@@ -408,9 +410,8 @@ hipError_t launch_hoist(const EvalLaunch &L, const Model &m, bool fold, float sc
                         const float *pipe, float *U, hipStream_t st)
 {
     if (L.nstages == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_hoist, dim3(L.nstages), dim3(64), 0, st, L, m.d->params, m.d->beta,
-                       fold ? 1 : 0, scale, pipe, U);
-    return hipGetLastError();
+    return launch_eval(k_hoist<QFEW>, k_hoist<QMAX>, dim3(L.nstages), dim3(64), st, L, m.d->params,
+                       m.d->beta, fold ? 1 : 0, scale, pipe, U);
 }
 
 hipError_t launch_step_hoist(const StepHead *h, const StepQ *qs, const Model &m,
@@ -438,9 +439,8 @@ hipError_t launch_eval_fp32(const EvalLaunch &L, const Model &m, const float *sc
     if (L.ntasks == 0) return hipSuccess;
     // two workgroups of 8 waves fill a compute unit (4 waves per SIMD)
     const int grid = std::min(L.ntasks, 2 * m.cus);
-    hipLaunchKernelGGL(k_eval_fp32, dim3(grid), dim3(F32_WAVES * 64), 0, st, L, &m.d->fp32, sched,
-                       terms, U, cost, stage);
-    return hipGetLastError();
+    return launch_eval(k_eval_fp32<QFEW>, k_eval_fp32<QMAX>, dim3(grid), dim3(F32_WAVES * 64), st,
+                       L, &m.d->fp32, sched, terms, U, cost, stage);
 }
 
 }  // namespace cm
