@@ -68,7 +68,7 @@ enum {
 
 /* Arithmetic of an evaluation.
  *   CM_FP32: schedule features stored as float32 raw values; every step in
- *            float32 on the vector ALUs.
+ *            float32 on the float32 matrix cores.
  *   CM_BF16: schedule features stored as bfloat16 raw values (2 bytes);
  *            the two dense layers run on bf16 matrix cores with float32
  *            accumulation, each product split into high and low bf16 parts

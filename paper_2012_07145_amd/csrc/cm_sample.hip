@@ -23,7 +23,7 @@
 //   5. k_s_write places the kept options in index order and empties the
 //      slots for the next call.
 // Bound by latency and scattered access: five dependent kernels of 3 to 10 us.
-// 17 queries of 700,000 options in all: 44 us; the three stable radix sorts,
+// 17 queries of 700,000 options in all: 37 us; the three stable radix sorts,
 // two scans and eight small kernels (73 launches) that this replaced took
 // 508 us.  (Chunks of 2,048: 47 us.)
 #include <algorithm>
