@@ -134,19 +134,19 @@ cm_status check_step_batch(const cm_step &S, const cm_batch *b, const float *U, 
     return CM_OK;
 }
 
-// Whether every row tile of a batch should have all waves of a workgroup,
-// which share its stages.  Where the tiles are fewer than the compute units,
-// a wave's stages one after the other (1.0 us each in bf16) are the step: one
-// query of 20 x 200 takes 26.1 us with 10 stages a wave and 20.1 us with 3, 30
-// x 8,000 (250 tiles) 35.4 and 28.9, in FP8 20 x 200 21.0 and 16.8.  Beyond one
-// tile per compute unit the chip is filled either way and the waves that share
-// tiles only add workgroups: 33 x 12,000 (375 tiles) took 31.6 and 34.5 us.
-// Fewer than 4 stages saved do not pay the sums' second walk (3 x 200: 18.6 and
-// 20.4 us; 5 x 200, 4 saved: 19.6 and 17.8).
+// Whether every row tile of a batch that goes by value (the spread kernels take
+// no other) should have all waves of a workgroup, which share its stages.  Where
+// the tiles are fewer than the compute units, a wave's stages one after the
+// other (1.0 us each in bf16) are the step: one query of 20 x 200 takes 26.1 us
+// with 10 stages a wave and 20.1 us with 3, 30 x 8,000 (250 tiles) 35.4 and
+// 28.9, in FP8 20 x 200 21.0 and 16.8.  Beyond one tile per compute unit the
+// chip is filled either way and the waves that share tiles only add workgroups:
+// 33 x 12,000 (375 tiles) took 31.6 and 34.5 us.  Fewer than 4 stages saved do
+// not pay the sums' second walk (3 x 200: 18.6 and 20.4 us; 5 x 200, 4 saved:
+// 19.6 and 17.8).
 bool spread_pays(const cm::StepReq *r, int nq, int max_tiles)
 {
     using namespace cm;
-    if (nq > STEP_VALUE_QUERIES) return false;
     int64_t tiles = 0;
     int chain = 0, shared = 0;  // most stages of a wave either way
     for (int q = 0; q < nq; ++q) {
@@ -162,7 +162,7 @@ bool spread_pays(const cm::StepReq *r, int nq, int max_tiles)
 // longest stage part first; each query's outputs stay where its request
 // points.
 void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm::StepReq *r,
-                      int nq, int32_t k, bool hoist, uint64_t *clk_out)
+                      int nq, int32_t k, bool hoist, bool value, uint64_t *clk_out)
 {
     using namespace cm;
     std::vector<int32_t> order(nq);
@@ -175,7 +175,7 @@ void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm
                      [&](int32_t x, int32_t y) { return per_wave(x) > per_wave(y); });
 
     const int gpt = S.cfg.group_tiles;
-    const bool spread = spread_pays(r, nq, S.cus);
+    const bool spread = value && spread_pays(r, nq, S.cus);
     std::memset(h, 0, sizeof *h);
     int64_t task = 0, row = 0, tile = 0;
     int32_t longest = 0;  // stages
@@ -235,6 +235,17 @@ hipError_t issue(const cm_step &S, Slot &sl, int n, hipStream_t st)
                        std::min(grid_of(S), head.ntasks), st);
 }
 
+// Whether a batch goes to the kernels by value: its descriptors fit their
+// arguments, and its rows the hoist's one workgroup each (a launch takes 2^32
+// threads; a loop over rows in that kernel cost 0.2 to 0.9 us).
+bool by_value(const cm::StepReq *r, int n)
+{
+    if (n > cm::STEP_VALUE_QUERIES) return false;
+    int64_t rows = 0;
+    for (int q = 0; q < n; ++q) rows += r[q].S;
+    return rows <= 1 << 22;
+}
+
 cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool hoist,
                         hipStream_t st, uint64_t *clk_out = nullptr)
 {
@@ -250,14 +261,15 @@ cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool
     // and 192, in FP8 136 and 128), and its launch 35 us of the caller's time
     // instead of 13, which a saturated server of 256 sessions feels: 1.55 to 1.64
     // G candidates/s so over three machines, 1.34 to 1.65 by replay.
-    if (n <= cm::STEP_VALUE_QUERIES) {
+    if (by_value(r, n)) {
         cm::StepArgs a;
-        fill_descriptors(S, &a.h, a.q, r, n, k, hoist, clk_out);
+        fill_descriptors(S, &a.h, a.q, r, n, k, hoist, true, clk_out);
         std::memset(a.q + n, 0, (cm::STEP_VALUE_QUERIES - n) * sizeof(cm::StepQ));
         CM_HIP(cm::launch_step_hoist(a, S.model->m, S.prec, st));
         CM_HIP(cm::launch_step(a, sl.d_ctl, sl.d_tpart, S.model->m, S.prec, grid_of(S), st));
     } else {
-        fill_descriptors(S, head_of(sl.h_block), queries_of(sl.h_block), r, n, k, hoist, clk_out);
+        fill_descriptors(S, head_of(sl.h_block), queries_of(sl.h_block), r, n, k, hoist, false,
+                         clk_out);
         CM_HIP(issue(S, sl, n, st));
     }
     CM_HIP(hipEventRecord(sl.done, st));
