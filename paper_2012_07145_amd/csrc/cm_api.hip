@@ -493,8 +493,15 @@ namespace {
 // Descriptors of queries [g0, g0 + ng) for one launch.  Hoisted rows of the
 // batch are laid out in batch order: query q's rows start at (sum of n_stages
 // of the queries before it) * 32 floats.
+// A launch of at most spread_tiles row tiles (one per compute unit; 0 for the
+// forms of the evaluators that do not spread) gives every tile all waves of a
+// workgroup, which share its stages, where that saves a wave 4 or more: 30 x
+// 6,400 takes 27.5 us with 15 stages a wave and 19.8 with 4, hoist and selection
+// included, 64 x 8,000 28.7 and 22.5, 64 x 2,000 27.2 and 20.0, in FP8 20.0 and
+// 19.2.  With more tiles the chip is filled either way, and fewer stages saved
+// do not pay the sums' second walk (both measured in steps: cm_step.hip).
 void fill_eval_launch(cm::EvalLaunch &L, const cm_batch *b, int32_t g0, int32_t ng,
-                      int64_t stage_prefix, cm_precision prec)
+                      int64_t stage_prefix, cm_precision prec, int spread_tiles = 0)
 {
     using namespace cm;
     std::memset(&L, 0, sizeof L);
@@ -503,12 +510,19 @@ void fill_eval_launch(cm::EvalLaunch &L, const cm_batch *b, int32_t g0, int32_t 
     // part first so the longest-running ones start earliest
     int64_t row_of[QMAX];
     int32_t order[QMAX];
-    int64_t r = 0;
+    int64_t r = 0, all_tiles = 0;
+    int32_t chain = 0, shared = 0;  // most stages of a wave without and with spreading
     for (int32_t j = 0; j < ng; ++j) {
+        const cm_query &Q = b->queries[g0 + j];
         row_of[j] = r;
-        r += b->queries[g0 + j].n_stages;
+        r += Q.n_stages;
         order[j] = j;
+        if (Q.n_cands == 0) continue;
+        all_tiles += cdiv(Q.n_cands, TILE_ROWS);
+        chain = std::max(chain, (int32_t)cdiv(Q.n_stages, stage_parts(Q.n_stages)));
+        shared = std::max(shared, (int32_t)cdiv(Q.n_stages, EVAL_WAVES));
     }
+    const bool spread = all_tiles <= spread_tiles && chain - shared >= 4;
     auto per_wave = [&](int32_t j) {
         const int S = b->queries[g0 + j].n_stages;
         return prec == CM_FP32 ? S : (S + stage_parts(S) - 1) / stage_parts(S);
@@ -529,7 +543,7 @@ void fill_eval_launch(cm::EvalLaunch &L, const cm_batch *b, int32_t g0, int32_t 
         e.u_off = (stage_prefix + row_of[j]) * H;
         e.hrow0 = (int32_t)hrow;
         e.task0 = (int32_t)task;
-        e.parts = stage_parts(Q.n_stages);
+        e.parts = spread ? EVAL_WAVES : stage_parts(Q.n_stages);
         e.stage_off = Q.terms_off / C;
         hrow += Q.n_stages;
         if (prec == CM_FP32) {
@@ -586,7 +600,8 @@ cm_status eval_impl(const cm_model *M, cm_precision prec, const cm_batch *b, con
     for (int32_t g0 = 0; g0 < b->n_queries; g0 += QMAX) {
         const int32_t ng = std::min<int32_t>(QMAX, b->n_queries - g0);
         EvalLaunch L;
-        fill_eval_launch(L, b, g0, ng, stage_prefix, prec);
+        fill_eval_launch(L, b, g0, ng, stage_prefix, prec,
+                         stage_out || ridx || prec == CM_FP32 ? 0 : M->m.cus);
         if (prec == CM_FP32)
             CM_HIP(launch_eval_fp32(L, M->m, (const float *)b->sched, b->terms, U, cost_out,
                                     stage_out, s));

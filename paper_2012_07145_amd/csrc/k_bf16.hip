@@ -9,11 +9,12 @@ namespace {
 
 using namespace bf16eval;
 
-template <bool kStage, bool kIndexed, int kQ>
-__global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_eval_bf16(
-    EvalLaunchOf<kQ> L, const Bf16Pack *__restrict__ pk, const uint16_t *sched, const float *terms,
-    const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage,
-    const int32_t *__restrict__ ridx, uint32_t rows)
+template <bool kStage, bool kIndexed, bool kSpread, int kQ>
+__device__ __forceinline__ void eval_body(const EvalLaunchOf<kQ> &L,
+                                          const Bf16Pack *__restrict__ pk, const uint16_t *sched,
+                                          const float *terms, const float *__restrict__ U,
+                                          float *__restrict__ cost, float *__restrict__ stage,
+                                          const int32_t *__restrict__ ridx, uint32_t rows)
 {
     __shared__ GroupShared sh;
     __shared__ uint32_t tab[LOG_N];
@@ -34,11 +35,35 @@ __global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu
     Q.stage = kStage ? stage + E.stage_off : nullptr;
     Q.S = E.S;
     Q.N = E.N;
-    Q.P = E.parts;
+    Q.P = kSpread ? stage_parts(E.S) : E.parts;
     const Weights w = load_weights(pk, lane);
     const Pairs kp = make_pairs();
     __syncthreads();  // the table is in LDS
-    eval_group<false, kStage, kIndexed>(Q, blockIdx.x - E.task0, wave, lane, w, kp, tab, sh);
+    const int group = blockIdx.x - E.task0;
+    if (kSpread && Q.P < E.parts)
+        eval_group<false, false, false, kSpread>(Q, group, wave, lane, w, kp, tab, sh);
+    else
+        eval_group<false, kStage, kIndexed>(Q, group, wave, lane, w, kp, tab, sh);
+}
+
+template <bool kStage, bool kIndexed, int kQ>
+__global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_eval_bf16(
+    EvalLaunchOf<kQ> L, const Bf16Pack *__restrict__ pk, const uint16_t *sched, const float *terms,
+    const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage,
+    const int32_t *__restrict__ ridx, uint32_t rows)
+{
+    eval_body<kStage, kIndexed, false>(L, pk, sched, terms, U, cost, stage, ridx, rows);
+}
+
+// Launches of at most one workgroup per compute unit, whose tiles take all
+// their waves: twice the registers.
+template <int kQ>
+__global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_eval_bf16_spread(
+    EvalLaunchOf<kQ> L, const Bf16Pack *__restrict__ pk, const uint16_t *sched, const float *terms,
+    const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage,
+    const int32_t *__restrict__ ridx, uint32_t rows)
+{
+    eval_body<false, false, true>(L, pk, sched, terms, U, cost, stage, ridx, rows);
 }
 
 __global__ __launch_bounds__(256) void k_log_table(Bf16Pack *pk)
@@ -69,6 +94,9 @@ hipError_t launch_eval_bf16(const EvalLaunch &L, const Model &m, const uint16_t 
     if (ridx && stage) return go(k_eval_bf16<true, true, QFEW>, k_eval_bf16<true, true, QMAX>);
     if (ridx) return go(k_eval_bf16<false, true, QFEW>, k_eval_bf16<false, true, QMAX>);
     if (stage) return go(k_eval_bf16<true, false, QFEW>, k_eval_bf16<true, false, QMAX>);
+    for (int q = 0; q < L.nq; ++q)
+        if (L.q[q].parts > stage_parts(L.q[q].S))
+            return go(k_eval_bf16_spread<QFEW>, k_eval_bf16_spread<QMAX>);
     return go(k_eval_bf16<false, false, QFEW>, k_eval_bf16<false, false, QMAX>);
 }
 

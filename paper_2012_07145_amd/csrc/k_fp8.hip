@@ -11,11 +11,12 @@ namespace {
 
 using namespace fp8eval;
 
-template <bool kStage, bool kIndexed, int kQ>
-__global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_eval_fp8(
-    EvalLaunchOf<kQ> L, const Fp8Pack *__restrict__ pk, const uint8_t *codes, const float *terms,
-    const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage,
-    const int32_t *__restrict__ ridx, uint32_t rows)
+template <bool kStage, bool kIndexed, bool kSpread, int kQ>
+__device__ __forceinline__ void eval_body(const EvalLaunchOf<kQ> &L,
+                                          const Fp8Pack *__restrict__ pk, const uint8_t *codes,
+                                          const float *terms, const float *__restrict__ U,
+                                          float *__restrict__ cost, float *__restrict__ stage,
+                                          const int32_t *__restrict__ ridx, uint32_t rows)
 {
     __shared__ bf16eval::GroupShared sh;
     const int lane = threadIdx.x & 63;
@@ -33,9 +34,31 @@ __global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu
     Q.stage = kStage ? stage + E.stage_off : nullptr;
     Q.S = E.S;
     Q.N = E.N;
-    Q.P = E.parts;
+    Q.P = kSpread ? stage_parts(E.S) : E.parts;
     const Weights8 w = load_weights8(pk, lane);
-    eval_group8<false, kStage, kIndexed>(Q, blockIdx.x - E.task0, wave, lane, w, sh);
+    const int group = blockIdx.x - E.task0;
+    if (kSpread && Q.P < E.parts)
+        eval_group8<false, false, false, kSpread>(Q, group, wave, lane, w, sh);
+    else
+        eval_group8<false, kStage, kIndexed>(Q, group, wave, lane, w, sh);
+}
+
+template <bool kStage, bool kIndexed, int kQ>
+__global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_eval_fp8(
+    EvalLaunchOf<kQ> L, const Fp8Pack *__restrict__ pk, const uint8_t *codes, const float *terms,
+    const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage,
+    const int32_t *__restrict__ ridx, uint32_t rows)
+{
+    eval_body<kStage, kIndexed, false>(L, pk, codes, terms, U, cost, stage, ridx, rows);
+}
+
+template <int kQ>
+__global__ __launch_bounds__(EVAL_WAVES * 64) __attribute__((amdgpu_waves_per_eu(4, 4))) void k_eval_fp8_spread(
+    EvalLaunchOf<kQ> L, const Fp8Pack *__restrict__ pk, const uint8_t *codes, const float *terms,
+    const float *__restrict__ U, float *__restrict__ cost, float *__restrict__ stage,
+    const int32_t *__restrict__ ridx, uint32_t rows)
+{
+    eval_body<false, false, true>(L, pk, codes, terms, U, cost, stage, ridx, rows);
 }
 
 // e4m3 code of v: NaN -> 0x7F, magnitudes beyond 448 saturate (the
@@ -164,6 +187,9 @@ hipError_t launch_eval_fp8(const EvalLaunch &L, const Model &m, const uint8_t *c
     if (ridx && stage) return go(k_eval_fp8<true, true, QFEW>, k_eval_fp8<true, true, QMAX>);
     if (ridx) return go(k_eval_fp8<false, true, QFEW>, k_eval_fp8<false, true, QMAX>);
     if (stage) return go(k_eval_fp8<true, false, QFEW>, k_eval_fp8<true, false, QMAX>);
+    for (int q = 0; q < L.nq; ++q)
+        if (L.q[q].parts > stage_parts(L.q[q].S))
+            return go(k_eval_fp8_spread<QFEW>, k_eval_fp8_spread<QMAX>);
     return go(k_eval_fp8<false, false, QFEW>, k_eval_fp8<false, false, QMAX>);
 }
 

@@ -41,3 +41,28 @@ def test_queries_of_a_batch_equal_the_query_alone(prec, n):
     for j in range(3):
         assert np.array_equal(together[j], np.concatenate([a[j] for a in alone]))
     model.close()
+
+
+SPREAD_SHAPES = [
+    [(5, 1)], [(8, 31)], [(16, 32)], [(17, 33)], [(32, 200)], [(33, 8192)], [(64, 8193)],
+    [(64, 257)], [(65, 40)], [(20, 4100), (3, 60), (64, 0), (120, 33)], [(9, 1), (8, 0)],
+    [(7 + 4 * j, 17 * j) for j in range(15)],
+]
+
+
+@pytest.mark.parametrize("prec", ["bf16", "fp8"])
+@pytest.mark.parametrize("shapes", SPREAD_SHAPES, ids=lambda s: "x".join(map(str, s[0])))
+def test_small_calls_spread_over_the_waves(prec, shapes):
+    """Calls of few row tiles, whose stages all waves of a workgroup share, against
+    the form with stage costs, which never does: the same bits, at the edges of
+    the stage split, of the tiles and of the rule (256 tiles)."""
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2012_07145_amd as cm
+    rng = np.random.default_rng(78)
+    queries = [draw_query(rng, S, N) for S, N in shapes]
+    model = cm.cm_model_create(model_params(bias=True))
+    cm.cm_model_prepare_fp8(model, 16.0, 8.0)
+    plain, with_stages, _ = _costs(cm, model, prec, queries)
+    assert np.array_equal(plain, with_stages)
+    model.close()
