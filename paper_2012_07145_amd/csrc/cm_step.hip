@@ -142,20 +142,25 @@ cm_status check_step_batch(const cm_step &S, const cm_batch *b, const float *U, 
 // 28.9, in FP8 20 x 200 21.0 and 16.8.  Beyond one tile per compute unit the
 // chip is filled either way and the waves that share tiles only add workgroups:
 // 33 x 12,000 (375 tiles) took 31.6 and 34.5 us.  Fewer than 4 stages saved do
-// not pay the sums' second walk (3 x 200: 18.6 and 20.4 us; 5 x 200, 4 saved:
-// 19.6 and 17.8).
-bool spread_pays(const cm::StepReq *r, int nq, int max_tiles)
+// not pay the sums' second walk on given rows (3 x 200: 18.6 and 20.4 us; 5 x
+// 200, 4 saved: 19.6 and 17.8), but do where the waves also take over the hoist:
+// 3 x 200 21.5 us with the hoist's kernel and 15.5 so, 4 x 8,000 26.7 and 22.3,
+// in FP8 3 x 200 19.9 and 13.5.
+bool spread_pays(const cm::StepReq *r, int nq, bool hoist, int max_tiles)
 {
     using namespace cm;
     int64_t tiles = 0;
     int chain = 0, shared = 0;  // most stages of a wave either way
+    int longest = 0;
     for (int q = 0; q < nq; ++q) {
         tiles += cdiv(r[q].N, TILE_ROWS);
+        longest = std::max(longest, r[q].S);
         if (r[q].N == 0) continue;
         chain = std::max<int>(chain, (int)cdiv(r[q].S, stage_parts(r[q].S)));
         shared = std::max<int>(shared, (int)cdiv(r[q].S, EVAL_WAVES));
     }
-    return tiles <= max_tiles && chain - shared >= 4;
+    return tiles <= max_tiles &&
+           (chain - shared >= 4 || (hoist && longest <= OWN_HOIST_STAGES));
 }
 
 // Descriptors of the queries into *h and qs.  Tasks are issued
@@ -175,7 +180,7 @@ void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm
                      [&](int32_t x, int32_t y) { return per_wave(x) > per_wave(y); });
 
     const int gpt = S.cfg.group_tiles;
-    const bool spread = value && spread_pays(r, nq, S.cus);
+    const bool spread = value && spread_pays(r, nq, hoist, S.cus);
     std::memset(h, 0, sizeof *h);
     int64_t task = 0, row = 0, tile = 0;
     int32_t longest = 0;  // stages

@@ -90,7 +90,7 @@ def test_step_by_value_and_by_block(cm, model, prec, graph):
 
 
 SPREAD_SHAPES = [
-    [(5, 1)], [(8, 31)], [(16, 32)], [(17, 33)], [(32, 200)], [(33, 8192)], [(64, 8193)],
+    [(1, 16)], [(3, 200)], [(4, 8192)], [(4, 8193)], [(5, 1)], [(8, 31)], [(16, 32)], [(17, 33)], [(32, 200)], [(33, 8192)], [(64, 8193)],
     [(64, 257)], [(65, 40)], [(20, 4100), (3, 60), (64, 0), (120, 33)], [(9, 0)],
     [(7 + 4 * j, 17 * j) for j in range(15)],
 ]
