@@ -458,7 +458,12 @@ cm_status cm_step_destroy(cm_step *step);
  * Asynchronous on `stream`.  The call waits on the host only when the slot
  * it reuses is still in flight (more than `slots` steps queued).  Calls on
  * one step are serialised; steps in flight on different streams use
- * different slots.  Errors: CM_EINVAL, CM_E2BIG (capacity, or a query above
+ * different slots.
+ * On a stream under capture the step is recorded with its descriptors, so a
+ * replay runs this batch whatever the step has run since.  A replay uses the
+ * step's device memory, which must therefore outlive the graph, and no slot is
+ * kept for it: order each replay against the step's other runs and replays (on
+ * one stream, or by events).  Errors: CM_EINVAL, CM_E2BIG (capacity, or a query above
  * cm_eval_batch's size limit), CM_EDEVICE. */
 cm_status cm_step_run(cm_step *step, const cm_batch *batch, const float *U, int32_t k,
                       float *cost_out, int32_t *idx_out, float *val_out, cm_stream stream);
@@ -494,7 +499,8 @@ cm_status cm_step_tuned_config(const cm_step *step, int32_t n_queries, int64_t r
  * persistent evaluation-and-selection kernel alone, without the descriptor
  * copy or the hoist): from the first of its workgroups to start to the last
  * to finish, read from the GPU's constant-rate real-time counter (100 MHz)
- * by the kernel itself.  Waits for that run to finish.  Errors: CM_EINVAL,
+ * by the kernel itself.  Waits for that run to finish.  Runs replayed from a
+ * graph are not waited for.  Errors: CM_EINVAL,
  * CM_ENOTFOUND (the step has not run), CM_EDEVICE. */
 cm_status cm_step_kernel_time(cm_step *step, float *us);
 

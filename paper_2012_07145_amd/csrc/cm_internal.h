@@ -362,11 +362,14 @@ hipError_t launch_step_hoist(const StepHead *h, const StepQ *qs, const Model &m,
                              cm_precision prec, int grid, hipStream_t st);
 hipError_t launch_step(const StepHead *h, const StepQ *qs, uint32_t *ctl, uint64_t *tpart,
                        const Model &m, cm_precision prec, int grid, hipStream_t st);
-// The same by value (a.h.nq <= STEP_VALUE_QUERIES).
+// Both by value (a.h.nq <= STEP_VALUE_QUERIES).
 hipError_t launch_step_hoist(const StepArgs &a, const Model &m, cm_precision prec,
                              hipStream_t st);
 hipError_t launch_step(const StepArgs &a, uint32_t *ctl, uint64_t *tpart, const Model &m,
                        cm_precision prec, int grid, hipStream_t st);
+// Writes `bytes` (a multiple of 8) of host memory, read before the call returns,
+// to dst on the stream.
+hipError_t launch_step_put(const void *src, size_t bytes, void *dst, hipStream_t st);
 
 // Device side: data one workgroup hands to another inside a launch (costs
 // read by the selecting workgroup, per-tile beam lists) is stored and loaded
@@ -403,6 +406,18 @@ __device__ inline int query_at(int n, int t, Start start_of)
     const int lane = (int)threadIdx.x & 63;
     const bool at = start_of(min(lane, n - 1)) <= t && lane < n;
     return __builtin_amdgcn_readfirstlane(__popcll(__ballot(at)) - 1);
+}
+
+// Host side: whether work issued to the stream is recorded into a graph.  Where
+// the stream cannot be asked, the launches themselves report the error.
+inline bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return status != hipStreamCaptureStatusNone;
 }
 
 // Host side: record a thread-local error message and return `st`.

@@ -56,6 +56,9 @@ size_t ctl_words(const cm_step &S) { return (size_t)cm::CTL_TCNT + (size_t)S.max
 
 int grid_of(const cm_step &S) { return S.cfg.grid > 0 ? S.cfg.grid : 2 * S.cus; }
 
+static_assert(sizeof(cm::StepHead) % sizeof(uint64_t) == 0 &&
+                  sizeof(cm::StepQ) % sizeof(uint64_t) == 0,
+              "a block is whole 64-bit words");
 cm::StepHead *head_of(unsigned char *block) { return reinterpret_cast<cm::StepHead *>(block); }
 cm::StepQ *queries_of(unsigned char *block)
 {
@@ -221,16 +224,22 @@ void fill_descriptors(const cm_step &S, cm::StepHead *h, cm::StepQ *qs, const cm
     h->clk_out = clk_out;
 }
 
-// The device work of one step whose descriptors are in the slot's block: their
-// copy, hoist, step kernel.
-hipError_t issue(const cm_step &S, Slot &sl, int n, hipStream_t st)
+// The device work of one step whose descriptors are in a host block: their copy
+// into the slot's, hoist, step kernel.  A copy is taken from the block when it
+// runs, which for a recorded step is at every replay, when the block has long
+// been another step's; so a recorded step's descriptors go by value, as
+// arguments of the kernels that write them.
+hipError_t issue(const cm_step &S, Slot &sl, const unsigned char *block, int n, bool recorded,
+                 hipStream_t st)
 {
     using namespace cm;
     const StepHead *h = reinterpret_cast<const StepHead *>(sl.d_block);
     const StepQ *qs = reinterpret_cast<const StepQ *>(sl.d_block + sizeof(StepHead));
     const size_t bytes = sizeof(StepHead) + (size_t)n * sizeof(StepQ);
-    const StepHead &head = *head_of(sl.h_block);
-    hipError_t e = hipMemcpyAsync(sl.d_block, sl.h_block, bytes, hipMemcpyHostToDevice, st);
+    const StepHead &head = *reinterpret_cast<const StepHead *>(block);
+    hipError_t e = recorded
+                       ? launch_step_put(block, bytes, sl.d_block, st)
+                       : hipMemcpyAsync(sl.d_block, block, bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return e;
     if (head.nrows > 0 &&
         (e = launch_step_hoist(h, qs, S.model->m, S.prec, std::min(head.nrows, 4 * S.cus), st)) !=
@@ -256,8 +265,14 @@ cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool
 {
     if (n == 0) return CM_OK;
     Slot &sl = S.slot[S.next];
-    if (sl.pending) CM_HIP(hipEventSynchronize(sl.done));  // its descriptors are still read
-    sl.pending = false;
+    // On a stream under capture the step is recorded, not run: nothing is waited
+    // for, the slot's event stays that of its last run (an event recorded here
+    // would belong to the graph), and the slot is the next run's as before.
+    const bool recorded = cm::capturing(st);
+    if (!recorded) {
+        if (sl.pending) CM_HIP(hipEventSynchronize(sl.done));  // its descriptors are still read
+        sl.pending = false;
+    }
     // Up to as many descriptors as a kernel's arguments hold go to the kernels
     // by value: their copy and the kernel boundary after it take 8 to 9 us, 32
     // queries 66 us so and 70 us through the slot's block.  Both ways are plain
@@ -273,10 +288,13 @@ cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool
         CM_HIP(cm::launch_step_hoist(a, S.model->m, S.prec, st));
         CM_HIP(cm::launch_step(a, sl.d_ctl, sl.d_tpart, S.model->m, S.prec, grid_of(S), st));
     } else {
-        fill_descriptors(S, head_of(sl.h_block), queries_of(sl.h_block), r, n, k, hoist, false,
-                         clk_out);
-        CM_HIP(issue(S, sl, n, st));
+        std::vector<uint64_t> own;  // the slot's block may still be read by its last run
+        if (recorded) own.resize(S.block_bytes / sizeof(uint64_t));
+        unsigned char *block = recorded ? reinterpret_cast<unsigned char *>(own.data()) : sl.h_block;
+        fill_descriptors(S, head_of(block), queries_of(block), r, n, k, hoist, false, clk_out);
+        CM_HIP(issue(S, sl, block, n, recorded, st));
     }
+    if (recorded) return CM_OK;
     CM_HIP(hipEventRecord(sl.done, st));
     sl.pending = true;
     S.last = S.next;
