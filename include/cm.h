@@ -238,7 +238,11 @@ cm_status cm_eval_stages(const cm_model *model, cm_precision precision,
  * (device int32, room for n_cands) and their number to sel_count[q]
  * (device).  seeds is a host array of n_queries seeds.  Asynchronous on
  * `stream` (the descriptors of more than 64 queries are staged through pinned
- * memory); allocates nothing.  One sampler serves one stream at a time.
+ * memory); allocates no device memory.  One sampler serves one stream at a
+ * time.  On a stream under capture the call is recorded with its descriptors: a
+ * replay draws for the batch and seeds that were recorded, whatever the sampler
+ * has been called with since, and is ordered with its other calls like one of
+ * them.
  * Errors: CM_EINVAL (NULL pointer, bad descriptor, wrong device), CM_E2BIG
  * (more queries or options than the sampler holds), CM_ENOMEM (create),
  * CM_EDEVICE. */

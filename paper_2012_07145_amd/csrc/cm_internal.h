@@ -369,7 +369,7 @@ hipError_t launch_step(const StepArgs &a, uint32_t *ctl, uint64_t *tpart, const 
                        cm_precision prec, int grid, hipStream_t st);
 // Writes `bytes` (a multiple of 8) of host memory, read before the call returns,
 // to dst on the stream.
-hipError_t launch_step_put(const void *src, size_t bytes, void *dst, hipStream_t st);
+hipError_t launch_put(const void *src, size_t bytes, void *dst, hipStream_t st);
 
 // Device side: data one workgroup hands to another inside a launch (costs
 // read by the selecting workgroup, per-tile beam lists) is stored and loaded

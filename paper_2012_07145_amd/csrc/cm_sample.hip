@@ -29,6 +29,7 @@
 #include <algorithm>
 #include <cstring>
 #include <new>
+#include <vector>
 
 #include "cm_internal.h"
 
@@ -136,7 +137,9 @@ __device__ inline uint32_t chunk_insert(u64 *key, uint32_t *cnt, u64 h, bool &fr
 // Descriptors of a call of at most VALUE_Q queries, passed to the first kernel
 // by value; it leaves them in memory for the others.  Larger calls copy them
 // from pinned memory ahead of it, which costs a copy, the event that guards
-// the pinned block and the gaps around them: 5 us a call.
+// the pinned block and the gaps around them: 5 us a call.  A replay of a
+// recorded copy would read the block when it is another call's, so a recorded
+// call passes them as arguments whatever their number (launch_put).
 constexpr int VALUE_Q = 64;
 struct SampleArgs {
     SampleQ q[VALUE_Q];
@@ -556,6 +559,7 @@ __global__ __launch_bounds__(ST) void k_s_clear(Table tb, int64_t slots)
     }
 }
 
+static_assert(sizeof(SampleQ) % 8 == 0, "whole words for launch_put");
 static_assert(MASKS <= 64 && LSLOTS <= 65536, "one wave scans the masks, used[] holds slots");
 
 }  // namespace
@@ -571,7 +575,7 @@ struct cm_sampler {
     hipEvent_t staged = nullptr;  // the last copy out of h_q has been done
     unsigned char *d = nullptr;   // all device scratch
     cm::Table tb{};               // empty between calls
-    bool clean = true;            // tb is empty once the work queued so far ends
+    bool clean = true;            // tb is empty once the calls so far, recorded ones aside, end
     uint32_t *slot = nullptr;     // per option: its slot in the query's part of the table
     uint64_t *list = nullptr;     // candidates of the buckets
     cm::u64 *mask = nullptr;      // kept options, 64 per word
@@ -703,9 +707,15 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
     hipStream_t s = (hipStream_t)stream;
     const int nq = b->n_queries;
     const bool by_value = nq <= VALUE_Q;
+    // On a stream under capture the call is recorded, not run: the pinned block,
+    // its event and the table's state stay those of the last call.
+    const bool recorded = capturing(s);
     SampleArgs args;
-    SampleQ *const hq = by_value ? args.q : sp->h_q;
-    if (!by_value) CM_HIP(hipEventSynchronize(sp->staged));  // the last copy has left h_q
+    std::vector<SampleQ> own;
+    if (!by_value && recorded) own.resize(nq);
+    SampleQ *const hq = by_value ? args.q : recorded ? own.data() : sp->h_q;
+    if (!by_value && !recorded)
+        CM_HIP(hipEventSynchronize(sp->staged));  // the last copy has left h_q
     int64_t base = 0;
     int32_t chunks = 0, most = 0;
     for (int q = 0; q < nq; ++q) {
@@ -715,7 +725,9 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
         base += Q.n_cands;
         chunks += std::max(1, (int32_t)(((int64_t)Q.n_cands + CHUNK - 1) / CHUNK));
     }
-    if (!by_value) {
+    if (!by_value && recorded) {
+        CM_HIP(launch_put(hq, sizeof(SampleQ) * nq, sp->d_q, s));
+    } else if (!by_value) {
         CM_HIP(hipMemcpyAsync(sp->d_q, hq, sizeof(SampleQ) * nq, hipMemcpyHostToDevice, s));
         CM_HIP(hipEventRecord(sp->staged, s));
     }
@@ -736,7 +748,7 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
                            sp->slots);
         CM_HIP(hipGetLastError());
     }
-    sp->clean = false;
+    if (!recorded) sp->clean = false;
     const dim3 g(chunks);
     if (by_value)
         hipLaunchKernelGGL(k_s_insert<true>, g, t, 0, s, args, sp->d_q, nq, hashes, sp->tb,
@@ -757,7 +769,7 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
     hipLaunchKernelGGL(k_s_write, g, t, 0, s, sp->d_q, nq, chunks, sp->tb, sp->slot, sp->mask,
                        sp->kept, sel_idx, sel_count);
     CM_HIP(hipGetLastError());
-    sp->clean = true;
+    if (!recorded) sp->clean = true;
     return CM_OK;
 }
 

@@ -238,7 +238,7 @@ hipError_t issue(const cm_step &S, Slot &sl, const unsigned char *block, int n, 
     const size_t bytes = sizeof(StepHead) + (size_t)n * sizeof(StepQ);
     const StepHead &head = *reinterpret_cast<const StepHead *>(block);
     hipError_t e = recorded
-                       ? launch_step_put(block, bytes, sl.d_block, st)
+                       ? launch_put(block, bytes, sl.d_block, st)
                        : hipMemcpyAsync(sl.d_block, block, bytes, hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return e;
     if (head.nrows > 0 &&

@@ -273,28 +273,28 @@ k_step_fp8_spread(StepArgs a, uint32_t *ctl, uint64_t *tpart, const Fp8Pack *__r
     step_body<true, kOwn>(&a.h, a.q, ctl, tpart, pk, hp);
 }
 
-// Words of host memory as arguments (descriptors of a recorded step: a replay
+// Words of host memory as arguments (descriptors of a recorded call: a replay
 // takes its arguments from the graph).
 struct PutArgs {
     uint64_t w[NT - 64];
 };
 static_assert(sizeof(PutArgs) <= 4096 - 64, "kernel arguments");
 
-__global__ __launch_bounds__(NT) void k_step_put(PutArgs a, int n, uint64_t *__restrict__ dst)
+__global__ __launch_bounds__(NT) void k_put(PutArgs a, int n, uint64_t *__restrict__ dst)
 {
     if ((int)threadIdx.x < n) dst[threadIdx.x] = a.w[threadIdx.x];
 }
 
 }  // namespace
 
-hipError_t launch_step_put(const void *src, size_t bytes, void *dst, hipStream_t st)
+hipError_t launch_put(const void *src, size_t bytes, void *dst, hipStream_t st)
 {
     constexpr size_t PART = sizeof(PutArgs);
     for (size_t at = 0; at < bytes; at += PART) {
         PutArgs a{};
         const size_t n = std::min(PART, bytes - at);
         std::memcpy(a.w, static_cast<const unsigned char *>(src) + at, n);
-        hipLaunchKernelGGL(k_step_put, dim3(1), dim3(NT), 0, st, a, (int)(n / sizeof(uint64_t)),
+        hipLaunchKernelGGL(k_put, dim3(1), dim3(NT), 0, st, a, (int)(n / sizeof(uint64_t)),
                            reinterpret_cast<uint64_t *>(static_cast<unsigned char *>(dst) + at));
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
