@@ -104,3 +104,22 @@ def test_sample_many_queries_some_empty(cm, oracle_mod):
         sel, cnt, descs = run(cm, sp, hs, ss)
         check(oracle_mod, hs, ss, sel, cnt, descs)
     sp.close()
+
+
+@pytest.mark.parametrize("nq", [4095, 4096, 4097, 9001])
+def test_sample_thousands_of_queries(cm, oracle_mod, nq):
+    """A chunk finds its query by votes over 64 of them at a time: the edges of
+    two and three rounds, with empty queries at both ends and in between."""
+    rng = np.random.default_rng(nq)
+    sizes = rng.integers(0, 4, nq)
+    sizes[rng.integers(0, nq, 40)] = rng.integers(1000, 3100, 40)
+    sizes[[0, nq - 1]] = 0
+    sizes[[1, 64, 4094, nq - 2]] = [1025, 2048, 1500, 1024]
+    pool = rng.integers(0, 2 ** 64, 900, dtype=np.uint64)
+    hashes = [rng.choice(pool[: max(1, n // 3)], n) for n in sizes]
+    seeds = rng.integers(0, 2 ** 64, nq, dtype=np.uint64)
+    sp = cm.cm_sampler_create(nq, int(sizes.sum()))
+    sel, cnt, descs = run(cm, sp, hashes, seeds)
+    check(oracle_mod, hashes, seeds, sel, cnt, descs)
+    assert sel[-1] == -5
+    sp.close()
