@@ -49,6 +49,7 @@ constexpr int PER = 2;                 // options per thread
 constexpr int CHUNK = ST * PER;        // options per chunk
 constexpr int MASKS = CHUNK / 64;      // 64-option masks per chunk
 constexpr int LSLOTS = 2 * CHUNK;      // slots of a chunk's LDS table
+constexpr int GROUP = 512;             // chunks whose kept options are also summed together
 constexpr int AT = 1024;               // threads per block of k_s_alloc
 constexpr int LIST_MAX = 256;          // entries of a bucket's list
 constexpr int LIST_ALL = 32;           // buckets of at most this many list every member
@@ -396,10 +397,29 @@ __global__ __launch_bounds__(ST) void k_s_rank(const SampleQ *__restrict__ q, in
     }
 }
 
+// What is kept in each GROUP of chunks, for k_s_write.
+static_assert(GROUP == ST, "one chunk per thread");
+__global__ __launch_bounds__(ST) void k_s_groups(const uint32_t *__restrict__ kept, int chunks,
+                                                 uint32_t *__restrict__ group)
+{
+    __shared__ uint32_t part[ST / 64];
+    const int t = threadIdx.x, e = blockIdx.x * GROUP + t;
+    const uint32_t sum = wave_scan(e < chunks ? kept[e] : 0);
+    if ((t & 63) == 63) part[t >> 6] = sum;
+    __syncthreads();
+    if (t == 0) {
+        uint32_t all = 0;
+#pragma unroll
+        for (int w = 0; w < ST / 64; ++w) all += part[w];
+        group[blockIdx.x] = all;
+    }
+}
+
 __global__ __launch_bounds__(ST) void k_s_write(const SampleQ *__restrict__ q, int nq, int chunks,
                                                 Table tb, const uint32_t *__restrict__ slot,
                                                 const u64 *__restrict__ mask,
                                                 const uint32_t *__restrict__ kept,
+                                                const uint32_t *__restrict__ group,
                                                 int32_t *__restrict__ out,
                                                 int32_t *__restrict__ count)
 {
@@ -409,9 +429,19 @@ __global__ __launch_bounds__(ST) void k_s_write(const SampleQ *__restrict__ q, i
     const int c = blockIdx.x;
     const int qi = query_of_chunk(q, nq, c);
     const SampleQ Q = q[qi];
-    // representatives of the query's chunks ahead of this one
+    // Representatives of the query's chunks ahead of this one: by chunk up to two
+    // groups, so that smaller calls need no sums of groups; past them whole
+    // groups by their sums, or the work grows with the square of the options
+    // (2^27 options in one query: 2^17 chunks, 8.6e9 reads).
     uint32_t sum = 0;
-    for (int e = Q.chunk0 + t; e < c; e += ST) sum += kept[e];
+    int from = Q.chunk0;
+    if (c - from > 2 * GROUP) {
+        const int g0 = (from + GROUP - 1) / GROUP, g1 = c / GROUP;
+        for (int e = from + t; e < g0 * GROUP; e += ST) sum += kept[e];
+        for (int g = g0 + t; g < g1; g += ST) sum += group[g];
+        from = g1 * GROUP;
+    }
+    for (int e = from + t; e < c; e += ST) sum += kept[e];
     sum = wave_scan(sum);
     if (lane == 63) part[wave] = sum;
     if (wave == 0) {
@@ -585,6 +615,7 @@ struct cm_sampler {
     uint64_t *list = nullptr;     // candidates of the buckets
     cm::u64 *mask = nullptr;      // kept options, 64 per word
     uint32_t *kept = nullptr;     // per chunk
+    uint32_t *group = nullptr;    // per GROUP chunks
     uint32_t *arena = nullptr;    // list entries given out
 };
 
@@ -626,10 +657,12 @@ cm_status cm_sampler_create(int32_t max_queries, int64_t max_options, cm_sampler
     s->max_options = max_options;
     // the scratch, laid out from the widest element type down
     const int64_t T = max_options, chunks = T / CHUNK + max_queries;
+    const int64_t groups = chunks / GROUP + 1;
     s->slots = (2 * T + max_queries + 3) / 4 * 4;
     const size_t bytes = (size_t)s->slots * (sizeof(u64) + 3 * sizeof(int32_t)) +
                          (size_t)T * (sizeof(uint64_t) + sizeof(uint32_t)) +
-                         (size_t)chunks * (MASKS * sizeof(u64) + sizeof(uint32_t)) + 64;
+                         (size_t)chunks * (MASKS * sizeof(u64) + sizeof(uint32_t)) +
+                         (size_t)groups * sizeof(uint32_t) + 64;
     bool ok = hipHostMalloc((void **)&s->h_q, sizeof(SampleQ) * max_queries, 0) == hipSuccess &&
               hipMalloc((void **)&s->d_q, sizeof(SampleQ) * max_queries) == hipSuccess &&
               hipEventCreateWithFlags(&s->staged, hipEventDisableTiming) == hipSuccess &&
@@ -650,6 +683,7 @@ cm_status cm_sampler_create(int32_t max_queries, int64_t max_options, cm_sampler
         s->mask = (u64 *)take((size_t)chunks * MASKS * sizeof(u64));
         s->slot = (uint32_t *)take((size_t)T * sizeof(uint32_t));
         s->kept = (uint32_t *)take((size_t)chunks * sizeof(uint32_t));
+        s->group = (uint32_t *)take((size_t)groups * sizeof(uint32_t));
         s->arena = (uint32_t *)take(sizeof(uint32_t));
     }
     if (!ok) {
@@ -771,8 +805,13 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
     hipLaunchKernelGGL(k_s_rank, g, t, 0, s, sp->d_q, nq, sp->tb, sp->slot, sp->list, sp->mask,
                        sp->kept);
     CM_HIP(hipGetLastError());
+    if ((int64_t)most > (int64_t)2 * GROUP * CHUNK) {
+        hipLaunchKernelGGL(k_s_groups, dim3((chunks + GROUP - 1) / GROUP), t, 0, s, sp->kept,
+                           chunks, sp->group);
+        CM_HIP(hipGetLastError());
+    }
     hipLaunchKernelGGL(k_s_write, g, t, 0, s, sp->d_q, nq, chunks, sp->tb, sp->slot, sp->mask,
-                       sp->kept, sel_idx, sel_count);
+                       sp->kept, sp->group, sel_idx, sel_count);
     CM_HIP(hipGetLastError());
     if (!recorded) sp->clean = true;
     return CM_OK;

@@ -123,3 +123,22 @@ def test_sample_thousands_of_queries(cm, oracle_mod, nq):
     check(oracle_mod, hashes, seeds, sel, cnt, descs)
     assert sel[-1] == -5
     sp.close()
+
+
+# options of a query ahead, so that the second query's chunks start inside a
+# group of 512, on its edge and one after it
+@pytest.mark.parametrize("ahead", [1000, 511 * 1024, 512 * 1024, 512 * 1024 + 1])
+@pytest.mark.parametrize("chunks", [1024, 1025, 1026, 1700])
+def test_sample_many_chunks(cm, oracle_mod, ahead, chunks):
+    """A query of more than two groups of chunks: what is kept ahead of a chunk
+    is summed by groups."""
+    rng = np.random.default_rng(chunks)
+    sizes = [ahead, chunks * 1024 - 7, 3000]
+    hashes = [rng.integers(0, max(1, n // 3), n).astype(np.uint64) for n in sizes]
+    seeds = rng.integers(0, 2 ** 64, len(sizes), dtype=np.uint64)
+    sp = cm.cm_sampler_create(len(sizes), sum(sizes))
+    for _ in range(2):
+        sel, cnt, descs = run(cm, sp, hashes, seeds)
+        check(oracle_mod, hashes, seeds, sel, cnt, descs)
+        assert sel[-1] == -5
+    sp.close()
