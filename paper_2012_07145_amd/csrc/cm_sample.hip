@@ -49,6 +49,7 @@ constexpr int PER = 2;                 // options per thread
 constexpr int CHUNK = ST * PER;        // options per chunk
 constexpr int MASKS = CHUNK / 64;      // 64-option masks per chunk
 constexpr int LSLOTS = 2 * CHUNK;      // slots of a chunk's LDS table
+constexpr int32_t MAX_GRID = 1 << 22;  // workgroups of a launch, which takes under 2^32 threads
 constexpr int GROUP = 512;             // chunks whose kept options are also summed together
 constexpr int AT = 1024;               // threads per block of k_s_alloc
 constexpr int LIST_MAX = 256;          // entries of a bucket's list
@@ -153,6 +154,7 @@ struct SampleArgs {
 
 template <bool kByValue>
 __global__ __launch_bounds__(ST) void k_s_insert(SampleArgs args, SampleQ *__restrict__ dq, int nq,
+                                                 int chunk0,
                                                  const uint64_t *__restrict__ hashes, Table tb,
                                                  uint32_t *__restrict__ slot, uint32_t *arena)
 {
@@ -161,12 +163,12 @@ __global__ __launch_bounds__(ST) void k_s_insert(SampleArgs args, SampleQ *__res
     __shared__ uint32_t cnt[LSLOTS + 1];  // members, then the slot in the query's table
     __shared__ uint16_t used[CHUNK + 1];
     __shared__ uint32_t nused;
-    const int t = threadIdx.x;
-    if (blockIdx.x == 0 && t == 0) *arena = 0;
-    if (kByValue && blockIdx.x == 0 && t < nq) dq[t] = args.q[t];
-    const int qi = query_of_chunk(q, nq, blockIdx.x);
+    const int t = threadIdx.x, c = chunk0 + (int)blockIdx.x;
+    if (c == 0 && t == 0) *arena = 0;
+    if (kByValue && c == 0 && t < nq) dq[t] = args.q[t];
+    const int qi = query_of_chunk(q, nq, c);
     const SampleQ Q = q[qi];
-    const uint32_t i0 = (uint32_t)(blockIdx.x - Q.chunk0) * CHUNK;
+    const uint32_t i0 = (uint32_t)(c - Q.chunk0) * CHUNK;
     if (Q.n == 0) return;  // uniform: the query's one chunk is empty
     uint64_t h[PER];
 #pragma unroll
@@ -265,15 +267,16 @@ __global__ __launch_bounds__(AT) void k_s_alloc(Table tb, int64_t slots, uint32_
         }
 }
 
-__global__ __launch_bounds__(ST) void k_s_list(const SampleQ *__restrict__ q, int nq, Table tb,
+__global__ __launch_bounds__(ST) void k_s_list(const SampleQ *__restrict__ q, int nq, int chunk0,
+                                               Table tb,
                                                const uint32_t *__restrict__ slot,
                                                uint64_t *__restrict__ list)
 {
-    const int t = threadIdx.x;
-    const int qi = query_of_chunk(q, nq, blockIdx.x);
+    const int t = threadIdx.x, c = chunk0 + (int)blockIdx.x;
+    const int qi = query_of_chunk(q, nq, c);
     const SampleQ Q = q[qi];
     const int64_t s0 = slots_of(Q, qi);
-    const uint32_t i0 = (uint32_t)(blockIdx.x - Q.chunk0) * CHUNK;
+    const uint32_t i0 = (uint32_t)(c - Q.chunk0) * CHUNK;
     if (Q.n == 0) return;
     int64_t s[PER];
     int32_t B[PER];
@@ -301,7 +304,8 @@ constexpr int SHARE = 8;   // neighbouring threads that share a longer one
 // chain of waits for memory stays at a few per round (one thread per option
 // for all of them took 31 us instead of 11 us for 17 queries of 700,000
 // options).
-__global__ __launch_bounds__(ST) void k_s_rank(const SampleQ *__restrict__ q, int nq, Table tb,
+__global__ __launch_bounds__(ST) void k_s_rank(const SampleQ *__restrict__ q, int nq, int chunk0,
+                                               Table tb,
                                                const uint32_t *__restrict__ slot,
                                                const uint64_t *__restrict__ list,
                                                u64 *__restrict__ mask, uint32_t *__restrict__ kept)
@@ -315,13 +319,14 @@ __global__ __launch_bounds__(ST) void k_s_rank(const SampleQ *__restrict__ q, in
     __shared__ u64 ms[MASKS];
     __shared__ uint32_t ntodo;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int qi = query_of_chunk(q, nq, blockIdx.x);
+    const int c = chunk0 + (int)blockIdx.x;
+    const int qi = query_of_chunk(q, nq, c);
     const SampleQ Q = q[qi];
     const int64_t s0 = slots_of(Q, qi);
-    const uint32_t i0 = (uint32_t)(blockIdx.x - Q.chunk0) * CHUNK;
+    const uint32_t i0 = (uint32_t)(c - Q.chunk0) * CHUNK;
     if (Q.n == 0) {
-        if (t < MASKS) mask[(int64_t)blockIdx.x * MASKS + t] = 0;
-        if (t == 0) kept[blockIdx.x] = 0;
+        if (t < MASKS) mask[(int64_t)c * MASKS + t] = 0;
+        if (t == 0) kept[c] = 0;
         return;
     }
     if (t == 0) ntodo = 0;
@@ -389,11 +394,11 @@ __global__ __launch_bounds__(ST) void k_s_rank(const SampleQ *__restrict__ q, in
     __syncthreads();
     if (wave == 0) {
         const u64 m = lane < MASKS ? ms[lane] : 0;
-        if (lane < MASKS) mask[(int64_t)blockIdx.x * MASKS + lane] = m;
+        if (lane < MASKS) mask[(int64_t)c * MASKS + lane] = m;
         uint32_t all = (uint32_t)__popcll(m);
 #pragma unroll
         for (int d = 1; d < 64; d <<= 1) all += (uint32_t)__shfl_xor((int)all, d);
-        if (lane == 0) kept[blockIdx.x] = all;
+        if (lane == 0) kept[c] = all;
     }
 }
 
@@ -415,8 +420,9 @@ __global__ __launch_bounds__(ST) void k_s_groups(const uint32_t *__restrict__ ke
     }
 }
 
-__global__ __launch_bounds__(ST) void k_s_write(const SampleQ *__restrict__ q, int nq, int chunks,
-                                                Table tb, const uint32_t *__restrict__ slot,
+__global__ __launch_bounds__(ST) void k_s_write(const SampleQ *__restrict__ q, int nq, int chunk0,
+                                                int chunks, Table tb,
+                                                const uint32_t *__restrict__ slot,
                                                 const u64 *__restrict__ mask,
                                                 const uint32_t *__restrict__ kept,
                                                 const uint32_t *__restrict__ group,
@@ -426,7 +432,7 @@ __global__ __launch_bounds__(ST) void k_s_write(const SampleQ *__restrict__ q, i
     __shared__ uint32_t part[ST / 64], before[MASKS];
     __shared__ u64 ms[MASKS];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int c = blockIdx.x;
+    const int c = chunk0 + (int)blockIdx.x;
     const int qi = query_of_chunk(q, nq, c);
     const SampleQ Q = q[qi];
     // Representatives of the query's chunks ahead of this one: by chunk up to two
@@ -481,6 +487,7 @@ __global__ __launch_bounds__(ST) void k_s_write(const SampleQ *__restrict__ q, i
 // options 21.8 and 11.6 us.
 template <bool kByValue>
 __global__ __launch_bounds__(ST) void k_s_small(SampleArgs args, const SampleQ *__restrict__ dq,
+                                                int query0,
                                                 const uint64_t *__restrict__ hashes,
                                                 int32_t *__restrict__ out,
                                                 int32_t *__restrict__ count)
@@ -492,9 +499,10 @@ __global__ __launch_bounds__(ST) void k_s_small(SampleArgs args, const SampleQ *
     __shared__ uint32_t part[ST / 64], before[MASKS];
     __shared__ u64 ms[MASKS];
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const SampleQ Q = (kByValue ? args.q : dq)[blockIdx.x];
+    const int qi = query0 + (int)blockIdx.x;
+    const SampleQ Q = (kByValue ? args.q : dq)[qi];
     if (Q.n == 0) {
-        if (t == 0) count[blockIdx.x] = 0;
+        if (t == 0) count[qi] = 0;
         return;
     }
     uint64_t h[PER];
@@ -573,7 +581,7 @@ __global__ __launch_bounds__(ST) void k_s_small(SampleArgs args, const SampleQ *
         const uint32_t n = lane < MASKS ? (uint32_t)__popcll(ms[lane]) : 0;
         sum = wave_scan(n);
         if (lane < MASKS) before[lane] = sum - n;
-        if (lane == 63) count[blockIdx.x] = (int32_t)sum;
+        if (lane == 63) count[qi] = (int32_t)sum;
     }
     __syncthreads();
 #pragma unroll
@@ -772,14 +780,24 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
     }
 
     const dim3 t(ST);
+    // one workgroup per query or chunk, in as many launches as they take
+    auto launch = [](int32_t n, auto &&kernel) {
+        for (int64_t at = 0; at < n; at += MAX_GRID) {
+            kernel((int)at, dim3((unsigned)std::min<int64_t>(MAX_GRID, n - at)));
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    };
     if (most <= CHUNK) {
-        if (by_value)
-            hipLaunchKernelGGL(k_s_small<true>, dim3(nq), t, 0, s, args, sp->d_q, hashes, sel_idx,
-                               sel_count);
-        else
-            hipLaunchKernelGGL(k_s_small<false>, dim3(nq), t, 0, s, SampleArgs{}, sp->d_q, hashes,
-                               sel_idx, sel_count);
-        CM_HIP(hipGetLastError());
+        CM_HIP(launch(nq, [&](int at, dim3 g) {
+            if (by_value)
+                hipLaunchKernelGGL(k_s_small<true>, g, t, 0, s, args, sp->d_q, at, hashes, sel_idx,
+                                   sel_count);
+            else
+                hipLaunchKernelGGL(k_s_small<false>, g, t, 0, s, SampleArgs{}, sp->d_q, at, hashes,
+                                   sel_idx, sel_count);
+        }));
         return CM_OK;
     }
     if (!sp->clean) {  // an earlier call's launches failed
@@ -788,31 +806,34 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
         CM_HIP(hipGetLastError());
     }
     if (!recorded) sp->clean = false;
-    const dim3 g(chunks);
-    if (by_value)
-        hipLaunchKernelGGL(k_s_insert<true>, g, t, 0, s, args, sp->d_q, nq, hashes, sp->tb,
-                           sp->slot, sp->arena);
-    else
-        hipLaunchKernelGGL(k_s_insert<false>, g, t, 0, s, SampleArgs{}, sp->d_q, nq, hashes,
-                           sp->tb, sp->slot, sp->arena);
-    CM_HIP(hipGetLastError());
+    CM_HIP(launch(chunks, [&](int at, dim3 g) {
+        if (by_value)
+            hipLaunchKernelGGL(k_s_insert<true>, g, t, 0, s, args, sp->d_q, nq, at, hashes, sp->tb,
+                               sp->slot, sp->arena);
+        else
+            hipLaunchKernelGGL(k_s_insert<false>, g, t, 0, s, SampleArgs{}, sp->d_q, nq, at,
+                               hashes, sp->tb, sp->slot, sp->arena);
+    }));
     const int64_t slots = 2 * T + nq;
     hipLaunchKernelGGL(k_s_alloc, dim3((unsigned)((slots + 4 * AT - 1) / (4 * AT))), dim3(AT), 0,
                        s, sp->tb, slots, sp->arena);
     CM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_s_list, g, t, 0, s, sp->d_q, nq, sp->tb, sp->slot, sp->list);
-    CM_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_s_rank, g, t, 0, s, sp->d_q, nq, sp->tb, sp->slot, sp->list, sp->mask,
-                       sp->kept);
-    CM_HIP(hipGetLastError());
+    CM_HIP(launch(chunks, [&](int at, dim3 g) {
+        hipLaunchKernelGGL(k_s_list, g, t, 0, s, sp->d_q, nq, at, sp->tb, sp->slot, sp->list);
+    }));
+    CM_HIP(launch(chunks, [&](int at, dim3 g) {
+        hipLaunchKernelGGL(k_s_rank, g, t, 0, s, sp->d_q, nq, at, sp->tb, sp->slot, sp->list,
+                           sp->mask, sp->kept);
+    }));
     if ((int64_t)most > (int64_t)2 * GROUP * CHUNK) {
         hipLaunchKernelGGL(k_s_groups, dim3((chunks + GROUP - 1) / GROUP), t, 0, s, sp->kept,
                            chunks, sp->group);
         CM_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_s_write, g, t, 0, s, sp->d_q, nq, chunks, sp->tb, sp->slot, sp->mask,
-                       sp->kept, sp->group, sel_idx, sel_count);
-    CM_HIP(hipGetLastError());
+    CM_HIP(launch(chunks, [&](int at, dim3 g) {
+        hipLaunchKernelGGL(k_s_write, g, t, 0, s, sp->d_q, nq, at, chunks, sp->tb, sp->slot,
+                           sp->mask, sp->kept, sp->group, sel_idx, sel_count);
+    }));
     if (!recorded) sp->clean = true;
     return CM_OK;
 }

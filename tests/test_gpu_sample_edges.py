@@ -142,3 +142,46 @@ def test_sample_many_chunks(cm, oracle_mod, ahead, chunks):
         check(oracle_mod, hashes, seeds, sel, cnt, descs)
         assert sel[-1] == -5
     sp.close()
+
+
+@pytest.mark.parametrize("largest", [1, 2500])  # one kernel for the call, and several
+def test_sample_more_queries_than_a_launch_takes(cm, oracle_mod, largest):
+    """2^23 workgroups of 512 threads are more than one launch holds."""
+    import torch
+    from paper_2012_07145_amd import _lib
+    import ctypes
+    nq = (1 << 23) + 5
+    rng = np.random.default_rng(largest)
+    n = rng.integers(0, 2, nq).astype(np.int32)
+    big = [0, 12345, (1 << 22) - 1, 1 << 22, nq - 1]
+    n[big] = largest
+    off = np.zeros(nq, np.int64)
+    np.cumsum(n[:-1], out=off[1:])
+    total = int(n.sum())
+    names = [f for f, _ in _lib.cm_query._fields_]
+    q = np.zeros(nq, np.dtype({"names": names,
+                               "formats": [np.int32, np.int32] + [np.int64] * (len(names) - 2),
+                               "offsets": [getattr(_lib.cm_query, f).offset for f in names],
+                               "itemsize": ctypes.sizeof(_lib.cm_query)}))
+    q["n_stages"], q["n_cands"], q["cost_off"] = 1, n, off
+    z = torch.zeros(1, device="cuda")
+    batch = cm.Batch([], z, z, z)
+    batch.c.n_queries = nq
+    batch.c.queries = ctypes.cast(q.ctypes.data, type(batch.c.queries))
+    hashes = rng.integers(0, 50, total).astype(np.uint64)
+    seeds = rng.integers(0, 2 ** 64, nq, dtype=np.uint64)
+    sp = cm.cm_sampler_create(nq, total)
+    sel = torch.full((total + 1,), -5, dtype=torch.int32, device="cuda")
+    cnt = torch.full((nq,), -5, dtype=torch.int32, device="cuda")
+    cm.cm_sample_buckets(sp, batch, torch.from_numpy(hashes.view(np.int64)).cuda(), seeds, sel, cnt)
+    torch.cuda.synchronize()
+    sel, cnt = sel.cpu().numpy(), cnt.cpu().numpy()
+    small = np.ones(nq, bool)
+    small[big] = False
+    assert np.array_equal(cnt[small], n[small])  # a lone option is kept
+    assert not sel[off[small & (n == 1)]].any()
+    for j in big:
+        want = oracle_mod.sample(hashes[off[j]:off[j] + n[j]], int(seeds[j]))
+        assert cnt[j] == want.size
+        assert np.array_equal(sel[off[j]:off[j] + want.size], want)
+    sp.close()
