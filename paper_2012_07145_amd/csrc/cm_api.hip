@@ -777,17 +777,19 @@ cm_status cm_penalize_known_bad(const cm_batch *b, const uint64_t *hashes,
     if (cands == 0 || n_bad == 0) return CM_OK;
     if (!hashes || !cost) return fail(CM_EINVAL, "hashes or cost is NULL");
     hipStream_t s = (hipStream_t)stream;
-    for (int32_t g0 = 0; g0 < b->n_queries; g0 += QMAX) {
-        const int32_t ng = std::min<int32_t>(QMAX, b->n_queries - g0);
+    for (int32_t g0 = 0; g0 < b->n_queries;) {
         PenaltyLaunch L;
         std::memset(&L, 0, sizeof L);
-        L.nq = ng;
-        for (int32_t j = 0; j < ng; ++j) {
-            const cm_query &Q = b->queries[g0 + j];
-            L.q[j].N = Q.n_cands;
-            L.q[j].cost_off = Q.cost_off;
-            L.q[j].block0 = L.blocks;
-            L.blocks += (int32_t)cdiv(Q.n_cands, PENALTY_THREADS);
+        while (L.nq < QMAX && g0 < b->n_queries) {
+            const cm_query &Q = b->queries[g0];
+            const int32_t blocks = (int32_t)cdiv(Q.n_cands, PENALTY_THREADS);
+            if (L.nq && L.blocks + blocks > PENALTY_MAX_BLOCKS) break;
+            PenaltyQ &p = L.q[L.nq++];
+            p.N = Q.n_cands;
+            p.cost_off = Q.cost_off;
+            p.block0 = L.blocks;
+            L.blocks += blocks;
+            ++g0;
         }
         CM_HIP(launch_penalty(L, hashes, bad_sorted, n_bad, penalty, cost, s));
     }

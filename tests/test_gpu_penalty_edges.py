@@ -37,3 +37,30 @@ def test_penalty_set_sizes(oracle_mod, n_bad):
         want = oracle_mod.penalize(cc, hh, bad, 1234.5)
         assert np.array_equal(got[d[5]:d[5] + d[1]].view(np.uint32), want.view(np.uint32))
     assert got[-1] == 0.0
+
+
+def test_penalty_more_candidates_than_a_launch_takes():
+    """More than 2^32 candidates in one call: every query's first and last ones
+    are reached, and no other cost changes."""
+    import torch
+    import paper_2012_07145_amd as cm
+    sizes = [3, 2 ** 31 - 1, 0, 2 ** 31 - 1, 1000]
+    total, descs = 0, []
+    for n in sizes:
+        descs.append((1, n, 0, 0, 0, total))
+        total += n
+    if torch.cuda.mem_get_info()[0] < 14 * total:
+        pytest.skip("needs 60 GB of device memory")
+    bad = torch.tensor([5, 77], device="cuda")
+    h = torch.zeros(total, dtype=torch.int64, device="cuda")
+    c = torch.zeros(total, device="cuda")
+    hits = sorted({d[5] + e for d in descs if d[1] for e in (0, d[1] // 2, d[1] - 1)})
+    h[torch.tensor(hits, device="cuda")] = 77
+    z = torch.zeros(1, device="cuda")
+    cm.cm_penalize_known_bad(cm.Batch(descs, z, z, z), h, bad, 2.5, c)
+    found = torch.cat([torch.nonzero(p).view(-1) + j * (1 << 28)
+                       for j, p in enumerate(torch.split(c, 1 << 28))]).cpu().numpy()
+    assert np.array_equal(found, hits)
+    assert bool((c[torch.tensor(hits, device="cuda")] == 2.5).all())
+    del h, c
+    torch.cuda.empty_cache()
