@@ -161,7 +161,18 @@ cm_status Core::check_locked(int32_t sid, const cm_request *rq, std::string *err
 uint64_t Core::enqueue_locked(int32_t sid, const cm_request *rq)
 {
     const uint64_t id = next_ticket_++;
-    Req &r = reqs_[id];
+    Req *rec;
+    if (spare_.empty()) {
+        rec = &reqs_[id];
+    } else {
+        auto node = std::move(spare_.back());
+        spare_.pop_back();
+        node.key() = id;
+        rec = &reqs_.insert(std::move(node)).position->second;
+    }
+    Req &r = *rec;
+    r.state = St::Pending;
+    r.t_admit = r.t_done = 0;
     r.session = sid;
     r.N = rq->n_cands;
     r.k = rq->k;
@@ -209,6 +220,14 @@ cm_status Core::submit_batch(int32_t n, const int32_t *sessions, const cm_reques
     return CM_OK;
 }
 
+// The request's ticket is no longer known; its record goes to a later one.
+void Core::forget_locked(std::unordered_map<uint64_t, Req>::iterator it)
+{
+    const size_t most = (size_t)cfg_.max_pending + (size_t)cfg_.max_slots * cfg_.max_batch_queries;
+    auto node = reqs_.extract(it);
+    if (spare_.size() < most) spare_.push_back(std::move(node));
+}
+
 cm_status Core::poll_locked(uint64_t ticket, cm_result *out, std::string *err)
 {
     auto it = reqs_.find(ticket);
@@ -222,7 +241,7 @@ cm_status Core::poll_locked(uint64_t ticket, cm_result *out, std::string *err)
     case St::Admitted:
         return CM_EAGAIN;
     case St::Canceled:
-        reqs_.erase(it);
+        forget_locked(it);
         *err = "request " + std::to_string(ticket) + " was canceled";
         return CM_ECANCELED;
     case St::Failed:
@@ -242,7 +261,7 @@ cm_status Core::poll_locked(uint64_t ticket, cm_result *out, std::string *err)
     out->t_submit_us = r.t_submit;
     out->t_admit_us = r.t_admit;
     out->t_done_us = r.t_done;
-    reqs_.erase(it);
+    forget_locked(it);
     return CM_OK;
 }
 
@@ -322,7 +341,7 @@ cm_status Core::wait_all(int32_t n, const uint64_t *tickets, int32_t timeout_ms,
             } else if (it->second.state == St::Done || it->second.state == St::Canceled) {
                 rc = it->second.state == St::Done ? CM_OK : CM_ECANCELED;
                 if (rc != CM_OK) e = "request " + std::to_string(tickets[j]) + " was canceled";
-                reqs_.erase(it);
+                forget_locked(it);
             } else {
                 rc = CM_EDEVICE;
                 e = fault_msg_;

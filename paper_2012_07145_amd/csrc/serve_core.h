@@ -140,6 +140,7 @@ private:
     double now_us() const;
     cm_status check_locked(int32_t sid, const cm_request *rq, std::string *err);
     uint64_t enqueue_locked(int32_t sid, const cm_request *rq);
+    void forget_locked(std::unordered_map<uint64_t, Req>::iterator it);
     cm_status poll_locked(uint64_t ticket, cm_result *out, std::string *err);
     void set_fault_locked(const std::string &what);
     void retire_locked(int slot);
@@ -154,6 +155,13 @@ private:
     std::condition_variable cv_work_, cv_done_;
     std::vector<Session> sessions_;
     std::unordered_map<uint64_t, Req> reqs_;
+    // Records of forgotten requests with their beams' buffers, for the next ones
+    // (at most as many as can be queued and in flight together).  Three
+    // allocations per request, freed by another thread and all under the lock,
+    // cost 10 us or, as the heap happened to lie, 160 us for a micro-batch of 128:
+    // 20 steps of 256 sessions ran at 1.35 to 1.95 G candidates/s in FP8 and 1.46
+    // to 1.55 in bf16, with records kept at 2.5 to 2.6 and 1.62 to 1.63.
+    std::vector<std::unordered_map<uint64_t, Req>::node_type> spare_;
     std::deque<uint64_t> pending_;  // queued tickets, submission order
     Slot slot_[MAX_SLOTS];
     uint64_t next_ticket_ = 1;
