@@ -111,3 +111,38 @@ def test_fp32_log_has_the_bits_of_log1pf(mix):
     same = got["sched"].view(np.uint32) == got["pipe"].view(np.uint32)
     same |= np.isnan(got["sched"]) & np.isnan(got["pipe"])
     assert np.all(same), (x[~same][:5], got["sched"][~same][:5], got["pipe"][~same][:5])
+
+
+def test_fp32_log_has_the_bits_of_log1pf_for_every_feature_to_65536():
+    """The same over every float32 from 0 to 65,536, which takes in all values of
+    the short form: the logarithm of a schedule feature, routed to the cost,
+    against that of an algorithm feature, routed to the hoisted row."""
+    import torch
+    import paper_2012_07145_amd as cm
+    from tests import cmcases as cc
+    end = 0x47800000
+    n = 1 << 24
+    sched, pipe = torch.zeros(n, 40, device="cuda"), torch.zeros(n, 56, device="cuda")
+    terms = torch.zeros(n, 8, device="cuda")
+    terms[:, 0] = 1.0
+    cost, U = torch.empty(n, device="cuda"), torch.empty(n, 32, device="cuda")
+    by_sched, by_pipe = (cm.cm_model_create(cc.log_params(r)) for r in ("sched", "pipe"))
+    ws = cm.cm_workspace_create(1, 1, n, n, 1)
+    zero_pipe = torch.zeros(56, device="cuda")
+    one_stage = cm.Batch([(1, n, 0, 0, 0, 0)], zero_pipe, sched, terms)
+    stages = cm.Batch([(n, 0, 0, 0, 0, 0)], pipe, sched, terms)
+    for first in range(0, end, n):
+        bits = torch.arange(first, first + n, dtype=torch.int32, device="cuda").clamp_(max=end)
+        x = bits.view(torch.float32)
+        sched[:, 0] = x
+        pipe[:, 0] = x
+        cm.cm_eval_batch(by_sched, "fp32", one_stage, ws, cost)
+        cm.cm_hoist_stages(by_pipe, "fp32", stages, U)
+        off = torch.nonzero(cost.view(torch.int32) != U[:, 0].contiguous().view(torch.int32))
+        assert off.numel() == 0, (off.numel(), x[off[:5, 0]], cost[off[:5, 0]], U[off[:5, 0], 0])
+    assert bits.max() == end and abs(float(cost.max()) - np.log(65537.0)) < 1e-5
+    ws.close()
+    by_sched.close()
+    by_pipe.close()
+    del sched, pipe, terms, U
+    torch.cuda.empty_cache()
