@@ -17,15 +17,18 @@
 //   3. k_s_list puts the bucket's candidates there: all members of a bucket
 //      of at most 32, else those with keys under (2r + 16) / B of the range
 //      for r representatives (keys are uniform);
-//   4. k_s_rank ranks each candidate among its list.  A list that came out
-//      with fewer than r entries or more than it holds (about one bucket in
-//      10^8) is ranked by a walk over the query's options instead;
+//   4. k_s_rank ranks each candidate among its list.  A bucket whose list came
+//      out with fewer than r entries (the binomial tail gives 6 in 10^8 for
+//      2,048 members, where it is largest) or more than it holds (under 1 in
+//      10^50) is gathered again under a wider bound;
 //   5. k_s_write places the kept options in index order and empties the
 //      slots for the next call.
 // Bound by latency and scattered access: five dependent kernels of 3 to 10 us.
 // 17 queries of 700,000 options in all: 37 us; the three stable radix sorts,
 // two scans and eight small kernels (73 launches) that this replaced took
-// 508 us.  (Chunks of 2,048: 47 us.)
+// 508 us.  (Chunks of 2,048: 47 us.)  The tables are read and added to at
+// random, so queries whose table no cache holds lose that: one query of 2^20
+// options 0.22 ms (sorts 0.57), of 2^24 3.9 ms (3.3), of 2^27 39 ms (26).
 #include <algorithm>
 #include <cstring>
 #include <new>
@@ -312,12 +315,13 @@ __global__ __launch_bounds__(ST) void k_s_rank(const SampleQ *__restrict__ q, in
 {
     struct Long {
         uint64_t mine;  // (key, index)
-        uint32_t off;
-        uint16_t f, r;
+        uint32_t off;   // its list's first entry
+        uint16_t f, r;  // entries (0: the list does not hold; off is then the slot), kept ones
     };
     __shared__ Long todo[CHUNK];
     __shared__ u64 ms[MASKS];
-    __shared__ uint32_t ntodo;
+    __shared__ uint64_t found[CHUNK];
+    __shared__ uint32_t ntodo, nfound, odd;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int c = chunk0 + (int)blockIdx.x;
     const int qi = query_of_chunk(q, nq, c);
@@ -329,7 +333,7 @@ __global__ __launch_bounds__(ST) void k_s_rank(const SampleQ *__restrict__ q, in
         if (t == 0) kept[c] = 0;
         return;
     }
-    if (t == 0) ntodo = 0;
+    if (t == 0) ntodo = odd = 0;
     __syncthreads();
     int64_t s[PER];
     int32_t B[PER], f[PER];
@@ -352,11 +356,9 @@ __global__ __launch_bounds__(ST) void k_s_rank(const SampleQ *__restrict__ q, in
             const uint32_t k = option_key(Q.seed, i);
             const uint64_t mine = ((uint64_t)k << 32) | i;
             if (f[j] < r || f[j] > min(B[j], LIST_MAX)) {
-                int rank = 0;
-                for (uint32_t e = 0; e < (uint32_t)Q.n && rank < r; ++e)
-                    if (s0 + slot[Q.base + e] == s[j])
-                        rank += (((uint64_t)option_key(Q.seed, e) << 32) | e) < mine;
-                keep = rank < r;
+                todo[atomicAdd(&ntodo, 1u)] =
+                    Long{mine, (uint32_t)(s[j] - s0), 0, (uint16_t)r};
+                odd = 1;
             } else if (k <= key_bound(B[j], r)) {
                 if (f[j] <= DIRECT) {
                     uint64_t v[DIRECT];
@@ -389,9 +391,50 @@ __global__ __launch_bounds__(ST) void k_s_rank(const SampleQ *__restrict__ q, in
 #pragma unroll
         for (int d = 1; d < SHARE; d <<= 1) rank += __shfl_xor(rank, d);
         const uint32_t i = (uint32_t)L.mine - i0;
-        if (sub == 0 && rank < L.r) atomicOr(&ms[i >> 6], 1ull << (i & 63));
+        if (sub == 0 && L.f > 0 && rank < L.r) atomicOr(&ms[i >> 6], 1ull << (i & 63));
     }
     __syncthreads();
+    // Buckets whose list came out too short or too long, one after the other:
+    // all threads gather the members under a wider bound, and rank the chunk's.
+    // (A walk over the query by every option took 101 ms for one such bucket of
+    // 256 in 1 M options, the whole call so 0.84 ms.)
+    for (int e = 0; odd && e < n; ++e) {
+        const Long L = todo[e];
+        if (L.f > 0) continue;  // the same for all threads
+        const int members = tb.cnt[s0 + L.off];
+        const uint32_t bound = key_bound(members, L.r);
+        const uint32_t wide = bound < 1u << 30 ? 4 * bound : ~0u;
+        if (t == 0) nfound = 0;
+        __syncthreads();
+#pragma unroll 4
+        for (uint32_t i = t; i < (uint32_t)Q.n; i += ST) {
+            if (slot[Q.base + i] != L.off) continue;
+            const uint32_t k = option_key(Q.seed, i);
+            if (k > wide) continue;
+            const uint32_t at = atomicAdd(&nfound, 1u);
+            if (at < CHUNK) found[at] = ((uint64_t)k << 32) | i;
+        }
+        __syncthreads();
+        const int m = (int)nfound;
+        for (int x = e + t; x < n; x += ST) {
+            const Long M = todo[x];
+            if (M.f > 0 || M.off != L.off) continue;
+            int rank = 0;
+            if (m < L.r || m > CHUNK) {  // not even then: a walk by this thread
+                for (uint32_t i = 0; i < (uint32_t)Q.n && rank < L.r; ++i)
+                    if (slot[Q.base + i] == L.off)
+                        rank += (((uint64_t)option_key(Q.seed, i) << 32) | i) < M.mine;
+            } else if ((uint32_t)(M.mine >> 32) > wide) {
+                rank = L.r;
+            } else {
+                for (int y = 0; y < m; ++y) rank += found[y] < M.mine;
+            }
+            const uint32_t i = (uint32_t)M.mine - i0;
+            if (rank < L.r) atomicOr(&ms[i >> 6], 1ull << (i & 63));
+            todo[x].f = 1;  // done; only this thread reads it before the barrier
+        }
+        __syncthreads();
+    }
     if (wave == 0) {
         const u64 m = lane < MASKS ? ms[lane] : 0;
         if (lane < MASKS) mask[(int64_t)c * MASKS + lane] = m;

@@ -185,3 +185,27 @@ def test_sample_more_queries_than_a_launch_takes(cm, oracle_mod, largest):
         assert cnt[j] == want.size
         assert np.array_equal(sel[off[j]:off[j] + want.size], want)
     sp.close()
+
+
+# (bucket size, its first option, seed), found as SHORT was: buckets over
+# several chunks
+SHORT_LONG = [(2048, 0, 91014303), (2048, 0, 20063815), (4096, 0, 16937571), (300, 900, 81182720)]
+
+
+@pytest.mark.parametrize("others", [0, 3000, 300_000])
+def test_sample_short_candidate_lists_over_chunks(cm, oracle_mod, others):
+    rng = np.random.default_rng(6)
+    hashes, seeds = [], []
+    for b, first, seed in SHORT_LONG + [(b, 0, s) for b, s in SHORT]:
+        h = np.concatenate([rng.integers(0, 40, first).astype(np.uint64) + np.uint64(100),
+                            np.full(b, 99, np.uint64), bucket_hashes(rng, others) if others else
+                            np.zeros(0, np.uint64)])
+        hashes.append(h)
+        seeds.append(seed)
+    seeds = np.array(seeds, np.uint64)
+    sp = cm.cm_sampler_create(len(hashes), sum(h.size for h in hashes))
+    for _ in range(2):
+        sel, cnt, descs = run(cm, sp, hashes, seeds)
+        check(oracle_mod, hashes, seeds, sel, cnt, descs)
+        assert sel[-1] == -5
+    sp.close()
