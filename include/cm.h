@@ -239,10 +239,12 @@ cm_status cm_eval_stages(const cm_model *model, cm_precision precision,
  * (device).  seeds is a host array of n_queries seeds.  Asynchronous on
  * `stream` (the descriptors of more than 64 queries are staged through pinned
  * memory); allocates no device memory.  One sampler serves one stream at a
- * time.  On a stream under capture the call is recorded with its descriptors: a
- * replay draws for the batch and seeds that were recorded, whatever the sampler
- * has been called with since, and is ordered with its other calls like one of
- * them.
+ * time: its scratch is handed from call to call, so calls that overlap on the
+ * device give wrong results, and so may every later call on that sampler
+ * (destroy it then).  On a stream under capture the call is recorded with its
+ * descriptors: a replay draws for the batch and seeds that were recorded,
+ * whatever the sampler has been called with since, and is ordered with its other
+ * calls like one of them.
  * Errors: CM_EINVAL (NULL pointer, bad descriptor, wrong device), CM_E2BIG
  * (more queries or options than the sampler holds), CM_ENOMEM (create),
  * CM_EDEVICE. */
