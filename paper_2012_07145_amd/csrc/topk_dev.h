@@ -20,16 +20,23 @@
 //   3. each compacted key is placed by counting the compacted keys below it
 //      (up to 8 threads share a key's count); keys placed at rank < k are the
 //      k best, already in order.
-// If more than FILT keys pass (many equal costs, costs in an order that
-// defeats the threshold, large k), a workgroup-wide bitwise radix search for
-// the exact k-th key takes the place of the threshold.
+// If many more than k keys pass (equal costs, costs in an order: the waves'
+// minima then say little about each other), a second threshold takes every
+// wave's minima from all over the tile, indices included (spread_threshold);
+// if more than FILT still pass (few threads hold all the smallest keys), a
+// workgroup-wide bitwise radix search finds the exact k-th key.
 // A query with several tiles has each tile's sorted k best written to a
 // device list; the last tile to finish selects again over those lists.
 // All of it is latency: a chain of about six barriers.  The threshold by a
 // bitonic sort of one 64-bit minimum per thread (36 exchanges, three of them
 // through LDS) that this replaced made the selection of 6,400 candidates
 // 18.5 us in two tiles of 4,096, against 5.7 us in one of 16,384, and
-// of 17 queries of up to 4,096 12.4 us against 6.5 us.
+// of 17 queries of up to 4,096 12.4 us against 6.5 us.  In random order, that is:
+// the sort gave every order the same time.  With the first threshold alone,
+// equal or sorted costs of one query of 4,096 took 24 to 36 us a call at k = 32
+// (the sort 7.6), of 100,000 34 to 43 (15.2), of 4,096 at k = 256 27 to 37
+// (10.7); with the second one 7.6, 17 and 14, and random ones, which do not come
+// to it, 7.5, 11.4 and 12.3 (8.8, 18.6 and 59.6).
 #pragma once
 
 #include "cm_internal.h"
@@ -40,8 +47,9 @@ namespace topk {
 constexpr uint64_t SENT = ~0ull;      // empty slot: ranks after every real key
 constexpr uint32_t EMPTY = ~0u;       // its cost half
 constexpr int FILT = 1024;            // compacted keys placed by counting
+constexpr int CHEAP = 256;            // more than 2k + this are worth a better threshold
 constexpr int ALL_PASS = 128;         // tiles of at most this many keys skip the threshold
-static_assert(FILT > CM_MAX_K && FILT >= 2 * CM_MAX_K, "a merge round makes progress, all may pass");
+static_assert(FILT >= 2 * CM_MAX_K + CHEAP, "a merge round makes progress, all may pass");
 
 // Order-preserving image of a cost.
 __device__ inline uint32_t cost_order(float c)
@@ -234,6 +242,74 @@ __device__ int place(int n, int k, TopkShared<NT> &sh)
     return min(n, k);
 }
 
+// The keys for which passes(cost order, j), compacted into sh.filt as far as
+// they fit (nfilt is 0 and visible): their number.  Ends with a barrier.
+template <int NT, int PER, class Index, class Passes>
+__device__ __forceinline__ int compact(const uint32_t (&ord)[PER], Index index, int nvalid,
+                                       Passes passes, TopkShared<NT> &sh)
+{
+    const int lane = sel_tid() & 63;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (j * NT >= nvalid) break;
+        mine += wave_count(passes(ord[j], j));
+    }
+    uint32_t base = reserve(sh, mine, lane);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (j * NT >= nvalid) break;
+        const bool p = passes(ord[j], j);
+        const uint64_t mask = __ballot(p);
+        const uint32_t pos = base + lanes_below(mask);
+        if (p && pos < FILT) sh.filt[pos] = make_key(ord[j], index(j));
+        base += (uint32_t)__popcll(mask);
+    }
+    __syncthreads();
+    return (int)sh.nfilt;
+}
+
+// A threshold with at least k keys at or under it, like the one of
+// tile_select, but for costs that are equal or in an order: every thread's
+// smallest key, index included, goes through LDS so that each wave holds every
+// WAVES-th of them, and the m smallest of a wave's 64 are taken one by one.
+// At most PER times as many keys pass as threads' minima do, which are k and a
+// few.  (More than k threads hold a key.)  Leaves nfilt 0.
+template <int NT, int PER, class Index>
+__device__ uint64_t spread_threshold(const uint32_t (&ord)[PER], Index index, int k,
+                                     TopkShared<NT> &sh)
+{
+    constexpr int W = NT / 64;
+    static_assert(NT <= FILT && W <= CM_MAX_K, "scratch in the lists");
+    const int t = sel_tid();
+    const int lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    // spreads the strided reads over the banks
+    auto at = [](int e) { return e ^ ((e >> 4) & 15); };
+    uint64_t key = make_key(ord[0], (uint32_t)index(0));
+#pragma unroll
+    for (int j = 1; j < PER; ++j)  // of equal costs the first has the lowest index
+        if (ord[j] < (uint32_t)(key >> 32)) key = make_key(ord[j], (uint32_t)index(j));
+    __syncthreads();  // the number of keys that passed is read
+    if (t == 0) sh.nfilt = 0;
+    sh.filt[at(t)] = key;
+    __syncthreads();
+    key = sh.filt[at(lane * W + wave)];
+    uint64_t w = 0;
+    for (int i = (k + W - 1) / W; i > 0; --i) {
+        const uint32_t hi = wave_min((uint32_t)(key >> 32));
+        const uint32_t lo = wave_min((uint32_t)(key >> 32) == hi ? (uint32_t)key : ~0u);
+        w = make_key(hi, lo);
+        if (key == w) key = SENT;
+    }
+    if (lane == 0) sh.best[wave] = w;
+    __syncthreads();
+    uint64_t T = 0;
+#pragma unroll
+    for (int j = 0; j < W; ++j) T = max(T, sh.best[j]);
+    return T;
+}
+
 // Select the k smallest keys of the workgroup into sh.best, ascending:
 // element j*NT + thread has cost order ord[j] and candidate index(j); the
 // nvalid first elements are real, the others EMPTY.  Returns min(k, nvalid).
@@ -268,25 +344,12 @@ __device__ int tile_select(const uint32_t (&ord)[PER], Index index, int nvalid, 
     } else {
         __syncthreads();
     }
-    // compact the keys at or under T
-    uint32_t mine = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        if (j * NT >= nvalid) break;
-        mine += wave_count(ord[j] <= T);
+    int n = compact(ord, index, nvalid, [&](uint32_t o, int) { return o <= T; }, sh);
+    if (n > CHEAP + 2 * k) {
+        const uint64_t T2 = spread_threshold(ord, index, k, sh);
+        n = compact(ord, index, nvalid,
+                    [&](uint32_t o, int j) { return make_key(o, (uint32_t)index(j)) <= T2; }, sh);
     }
-    uint32_t base = reserve(sh, mine, lane);
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        if (j * NT >= nvalid) break;
-        const bool p = ord[j] <= T;
-        const uint64_t mask = __ballot(p);
-        const uint32_t pos = base + lanes_below(mask);
-        if (p && pos < FILT) sh.filt[pos] = make_key(ord[j], index(j));
-        base += (uint32_t)__popcll(mask);
-    }
-    __syncthreads();
-    int n = (int)sh.nfilt;
     if (n > FILT) {
         const uint64_t T2 = block_threshold<NT, PER>(ord, index, k, sh);
         __syncthreads();
