@@ -209,9 +209,9 @@ struct FreezeLaunch {
     FreezeQ q[QMAX];
 };
 
-constexpr int PENALTY_THREADS = 256;  // candidates per workgroup
+constexpr int PENALTY_THREADS = 512;  // candidates per workgroup
 // Workgroups of a launch, which takes under 2^32 threads; a query has at most as many.
-constexpr int PENALTY_MAX_BLOCKS = 1 << 23;
+constexpr int PENALTY_MAX_BLOCKS = 1 << 22;
 static_assert(INT32_MAX / PENALTY_THREADS < PENALTY_MAX_BLOCKS, "one query fits a launch");
 
 struct PenaltyQ {

@@ -7,7 +7,6 @@
 namespace cm {
 namespace {
 
-
 constexpr int SAMPLES = 1024;  // hashes of the bad set kept in LDS
 
 // First position in a[0, n) (ascending) whose value is at least h.
@@ -31,7 +30,8 @@ __device__ inline int64_t lower_bound(const T *a, int64_t n, uint64_t h)
 // of the bad set goes to LDS first, so that the bisection waits for memory
 // only inside one step (not at all up to 1,024 hashes): 400 hashes and 17
 // queries, 6.2 us with a walk over the queries and the bisection in memory,
-// 4.1 us so.
+// 4.1 us so.  512 threads share the samples: with 256, 1 M candidates against
+// 100,000 hashes took 45.6 us a call (42.2 without samples, 39.3 so).
 __global__ __launch_bounds__(PENALTY_THREADS) void k_penalty(PenaltyLaunch L,
                                                              const uint64_t *__restrict__ hashes,
                                                              const uint64_t *__restrict__ bad,

@@ -64,3 +64,26 @@ def test_penalty_more_candidates_than_a_launch_takes():
     assert bool((c[torch.tensor(hits, device="cuda")] == 2.5).all())
     del h, c
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("n", [511, 512, 513, 1023, 1024, 1025])
+def test_penalty_workgroup_edges(oracle_mod, n):
+    import torch
+    import paper_2012_07145_amd as cm
+    rng = np.random.default_rng(n)
+    bad = np.sort(rng.integers(0, 2 ** 64, 1500, dtype=np.uint64))
+    descs, costs, hashes = [], [], []
+    for j in range(3):
+        descs.append((1, n, 0, 0, 0, j * n))
+        costs.append(rng.lognormal(8, 1, n).astype(np.float32))
+        hashes.append(np.where(rng.random(n) < 0.5, rng.choice(bad, n), bad[0] + np.uint64(1)))
+        hashes[-1][-1] = bad[-1]
+    z = torch.zeros(1, device="cuda")
+    c = torch.from_numpy(np.concatenate(costs)).cuda()
+    h = torch.from_numpy(np.concatenate(hashes).view(np.int64)).cuda()
+    cm.cm_penalize_known_bad(cm.Batch(descs, z, z, z), h,
+                             torch.from_numpy(bad.view(np.int64)).cuda(), -7.25, c)
+    got = c.cpu().numpy()
+    for j in range(3):
+        want = oracle_mod.penalize(costs[j], hashes[j], bad, -7.25)
+        assert np.array_equal(got[j * n:(j + 1) * n].view(np.uint32), want.view(np.uint32))
