@@ -47,9 +47,10 @@ namespace topk {
 constexpr uint64_t SENT = ~0ull;      // empty slot: ranks after every real key
 constexpr uint32_t EMPTY = ~0u;       // its cost half
 constexpr int FILT = 1024;            // compacted keys placed by counting
-constexpr int CHEAP = 256;            // more than 2k + this are worth a better threshold
+constexpr int CHEAP = 256;            // more than k + this are worth a better threshold
 constexpr int ALL_PASS = 128;         // tiles of at most this many keys skip the threshold
-static_assert(FILT >= 2 * CM_MAX_K + CHEAP, "a merge round makes progress, all may pass");
+static_assert(FILT >= 2 * CM_MAX_K && ALL_PASS <= CHEAP && CM_MAX_K <= CHEAP,
+              "a merge round makes progress, all may pass without a threshold");
 
 // Order-preserving image of a cost.
 __device__ inline uint32_t cost_order(float c)
@@ -345,7 +346,9 @@ __device__ int tile_select(const uint32_t (&ord)[PER], Index index, int nvalid, 
         __syncthreads();
     }
     int n = compact(ord, index, nvalid, [&](uint32_t o, int) { return o <= T; }, sh);
-    if (n > CHEAP + 2 * k) {
+    // random costs come to 1.7 k and 100 keys, sorted ones to 1,000; up to 512 are
+    // counted by two threads or more each
+    if (n > CHEAP + k) {
         const uint64_t T2 = spread_threshold(ord, index, k, sh);
         n = compact(ord, index, nvalid,
                     [&](uint32_t o, int j) { return make_key(o, (uint32_t)index(j)) <= T2; }, sh);

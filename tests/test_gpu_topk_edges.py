@@ -84,7 +84,7 @@ def test_topk_of_ordered_and_equal_costs(oracle_mod, kind, k):
     import paper_2012_07145_amd as cm
     rng = np.random.default_rng(k)
     z = torch.zeros(1, device="cuda")
-    sizes = [2 * k + 255, 2 * k + 256, 2 * k + 257, 1000, 4096, 9000, 16384, 40000]
+    sizes = [k + 255, k + 256, k + 257, 2 * k + 1, 1000, 4096, 9000, 16384, 40000]
     costs = [_ordered_costs(kind, n, rng) for n in sizes]
     descs, off = [], 0
     for c in costs:
