@@ -31,8 +31,8 @@
 // options 0.22 ms (sorts 0.57), of 2^24 3.9 ms (3.3), of 2^27 39 ms (26).
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <new>
-#include <vector>
 
 #include "cm_internal.h"
 
@@ -801,9 +801,10 @@ cm_status cm_sample_buckets(cm_sampler *sp, const cm_batch *b, const uint64_t *h
     // its event and the table's state stay those of the last call.
     const bool recorded = capturing(s);
     SampleArgs args;
-    std::vector<SampleQ> own;
-    if (!by_value && recorded) own.resize(nq);
-    SampleQ *const hq = by_value ? args.q : recorded ? own.data() : sp->h_q;
+    std::unique_ptr<SampleQ[]> own(!by_value && recorded ? new (std::nothrow) SampleQ[nq]
+                                                         : nullptr);
+    SampleQ *const hq = by_value ? args.q : recorded ? own.get() : sp->h_q;
+    if (!hq) return fail(CM_ENOMEM, "host allocation failed");
     if (!by_value && !recorded)
         CM_HIP(hipEventSynchronize(sp->staged));  // the last copy has left h_q
     int64_t base = 0;

@@ -288,9 +288,10 @@ cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool
         CM_HIP(cm::launch_step_hoist(a, S.model->m, S.prec, st));
         CM_HIP(cm::launch_step(a, sl.d_ctl, sl.d_tpart, S.model->m, S.prec, grid_of(S), st));
     } else {
-        std::vector<uint64_t> own;  // the slot's block may still be read by its last run
-        if (recorded) own.resize(S.block_bytes / sizeof(uint64_t));
-        unsigned char *block = recorded ? reinterpret_cast<unsigned char *>(own.data()) : sl.h_block;
+        // the slot's block may still be read by its last run
+        alignas(16) unsigned char own[sizeof(cm::StepHead) +
+                                      cm::STEP_MAX_QUERIES * sizeof(cm::StepQ)];
+        unsigned char *block = recorded ? own : sl.h_block;
         fill_descriptors(S, head_of(block), queries_of(block), r, n, k, hoist, false, clk_out);
         CM_HIP(issue(S, sl, block, n, recorded, st));
     }

@@ -23,6 +23,9 @@ int64_t request_bytes(cm_precision prec, int32_t S, int32_t N, int32_t k)
 Core::Core(const cm_server_cfg &cfg, Executor *ex) : cfg_(cfg), ex_(ex), t0_(Clock::now())
 {
     sessions_.resize(cfg.max_sessions);
+    // as many as can be queued and in flight together, and no more
+    spare_.reserve(std::min(SPARE, (size_t)cfg.max_pending +
+                                       (size_t)cfg.max_slots * cfg.max_batch_queries));
 }
 
 double Core::now_us() const
@@ -223,9 +226,8 @@ cm_status Core::submit_batch(int32_t n, const int32_t *sessions, const cm_reques
 // The request's ticket is no longer known; its record goes to a later one.
 void Core::forget_locked(std::unordered_map<uint64_t, Req>::iterator it)
 {
-    const size_t most = (size_t)cfg_.max_pending + (size_t)cfg_.max_slots * cfg_.max_batch_queries;
     auto node = reqs_.extract(it);
-    if (spare_.size() < most) spare_.push_back(std::move(node));
+    if (spare_.size() < spare_.capacity()) spare_.push_back(std::move(node));
 }
 
 cm_status Core::poll_locked(uint64_t ticket, cm_result *out, std::string *err)

@@ -156,11 +156,12 @@ private:
     std::vector<Session> sessions_;
     std::unordered_map<uint64_t, Req> reqs_;
     // Records of forgotten requests with their beams' buffers, for the next ones
-    // (at most as many as can be queued and in flight together).  Three
+    // (at most SPARE of them, in room reserved at creation).  Three
     // allocations per request, freed by another thread and all under the lock,
     // cost 10 us or, as the heap happened to lie, 160 us for a micro-batch of 128:
     // 20 steps of 256 sessions ran at 1.35 to 1.95 G candidates/s in FP8 and 1.46
     // to 1.55 in bf16, with records kept at 2.5 to 2.6 and 1.62 to 1.63.
+    static constexpr size_t SPARE = 16384;
     std::vector<std::unordered_map<uint64_t, Req>::node_type> spare_;
     std::deque<uint64_t> pending_;  // queued tickets, submission order
     Slot slot_[MAX_SLOTS];
