@@ -95,9 +95,6 @@ def parse():
     ap.add_argument("--no-fp8-serving", action="store_true",
                     help="skip the same serving workload in the FP8 form")
     ap.add_argument("--slots", type=int, default=3, help="serving micro-batches in flight")
-    ap.add_argument("--serve-graph", type=int, choices=(0, 1), default=None,
-                    help="use_graph of the server's step configuration, which the library "
-                         "keeps and reports; its steps are plain launches either way")
     ap.add_argument("--max-batch-queries", type=int, default=128)
     ap.add_argument("--copy-calibration", action="store_true",
                     help="only run a 1 GiB device copy (HBM counter calibration)")
@@ -217,8 +214,6 @@ def main():
     srv = cm.cm_server_create(model, k=K, arena_bytes=16 << 30, max_slots=args.slots,
                               max_pending=8192, max_sessions=SESSIONS, max_stages=128,
                               max_batch_queries=args.max_batch_queries, max_batch_cands=1 << 20)
-    if args.serve_graph is not None:
-        srv.set_step_config(0, 1, args.serve_graph)
     sids = [srv.session_open(pipe) for _, pipe, _ in sess_in]
 
     # a step's request j of every session, as pre-marshalled arrays

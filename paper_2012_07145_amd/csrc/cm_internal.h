@@ -111,8 +111,6 @@ struct Fp8Pack {
     float pad;
 };
 
-// Everything a model holds on the device from its creation, filled by one
-// copy (the log table by a kernel after it).
 // Operands of the hoist on the float32 matrix cores, laid out like Fp32Pack:
 // values 0..27: W_p rows 0..15 (14 steps), then 16..23; 28..39: W_1[:, :24]
 // rows 0..15 (6 steps), then 16..31.
@@ -123,6 +121,8 @@ struct HoistPack {
     float4 beta[8];
 };
 
+// Everything a model holds on the device from its creation, filled by one
+// copy (the log table by a kernel after it).
 struct ModelData {
     float params[N_PARAMS];  // float32 blob as given
     float beta[H];           // W_1[:, 24:] b_s, added when folding

@@ -279,8 +279,7 @@ cm_status launch_locked(cm_step &S, const cm::StepReq *r, int n, int32_t k, bool
     // launches: a graph of the same work took 7 us more for every batch, with 4
     // us at each of its edges (33 queries 77.5 us and 70.5, 128 hoisted ones 199
     // and 192, in FP8 136 and 128), and its launch 35 us of the caller's time
-    // instead of 13, which a saturated server of 256 sessions feels: 1.55 to 1.64
-    // G candidates/s so over three machines, 1.34 to 1.65 by replay.
+    // instead of 13.
     if (by_value(r, n)) {
         cm::StepArgs a;
         fill_descriptors(S, &a.h, a.q, r, n, k, hoist, true, clk_out);

@@ -3,11 +3,11 @@
 // in one launch.
 //
 // A grid of workgroups (8 waves each) whose size the batch may only reduce
-// takes tasks from a device-wide
-// queue (one atomic add per task, taken when the previous task ends).  A task is `gpt`
-// consecutive row-tile groups of one query, evaluated exactly as the
-// per-call kernels do (eval_bf16.h, eval_fp8.h), so the costs are
-// bit-identical to them.
+// takes tasks from a device-wide queue: a workgroup's first task is its own
+// number, and each further one costs an atomic add when the task before it
+// ends.  A task is `gpt` consecutive row-tile groups of one query, evaluated
+// exactly as the per-call kernels do (eval_bf16.h, eval_fp8.h), so the costs
+// are bit-identical to them.
 // Tasks never straddle a selection tile of TOPK_TILE candidates; the
 // workgroup whose task completes a tile (an arrival count per tile) selects
 // that tile's k best, and for a query of several tiles the last tile to
