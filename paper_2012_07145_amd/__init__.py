@@ -464,7 +464,8 @@ class Server:
 
     def wait_all_results(self, tickets, timeout_ms: int = 60000):
         """Wait for every ticket and release them; returns [(idx, val), ...]
-        in ticket order (each the request's beam)."""
+        in ticket order (each the request's beam; the beams are rows of two
+        arrays made by this call)."""
         t = np.ascontiguousarray(tickets, dtype=np.uint64)
         n = len(t)
         # one array of each kind for all beams, pointed into by numpy in one
